@@ -90,6 +90,12 @@ def tune(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver], candidates: Iter
     return dict(out, cached=False)
 
 
+# Stages that a merged launch runs in the default mode: not timed on their own,
+# their settings stand (or follow the group they share) and are reported.
+MERGED: Dict[str, Tuple[str, ...]] = {
+    "riemann_xyz": ("riemann_x", "riemann_y", "riemann_z"),
+    "trans2_xyz": ("trans2_x", "trans2_y", "trans2_z"),
+}
 STAGE_CANDIDATES: Tuple[int, ...] = (1, 2, 4, 8)
 
 
@@ -154,6 +160,8 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
         for st, p in before.items():
             ctx.set_stage_planes(st, p)
         planes = dict(before)
+    for st in start:
+        planes.update({m: ctx.stage_planes(m)[0] for m in MERGED.get(st, ())})
     out = {"planes": planes, "ms_per_step": min(tuned, base_total), "start_ms_per_step": base_total,
            "trials": {str(p): t for p, t in trials.items()}, "signature": key,
            "when": time.strftime("%Y-%m-%dT%H:%M:%S")}

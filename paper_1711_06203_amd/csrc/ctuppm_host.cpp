@@ -195,8 +195,8 @@ struct ctuppm_ctx {
   // waves forms, times their zseg:
   // cons->prim two (each thread converts two independent cells), the merged
   // tracing four (measured: 2.31 -> 2.13 ms at KH 256^3), the rest one
-  int region_planes[kNumRegions] = {1, 2, 1, 1, 1, 1, 1, 1, 1, 4};
-  static_assert(kNumRegions == 10 && kGrown == 1 && kCells1T == 9, "one default per work region");
+  int region_planes[kNumRegions] = {1, 2, 1, 1, 1, 1, 1, 1, 1, 4, 1};
+  static_assert(kNumRegions == 11 && kGrown == 1 && kCells1T == 9, "one default per work region");
   bool region_set[kNumRegions] = {};  // set by the caller: used as given (defaults adapt to the level size)
   int fused = 1;          // CTU cell stages: tracing and stage 1 of the three directions in one kernel each
   std::vector<Staging> staging;
@@ -453,6 +453,8 @@ int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool per
   Launch L{};
   L.segs = G;
   L.grid = grid_for(c, G.beg[G.n], persistent);
+  // the merged normal and final fluxes visit their units once per direction
+  if (stage == kStRiem3 || stage == kStT2All) L.grid *= 3;
   L.stream = s;
   L.arr = A.arr;
   L.out = A.out;
@@ -1186,12 +1188,12 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
 
 // Cell stages of a CTU step after cons->prim: one kernel per direction, or
 // (fused, the default) the flattening with the tracing of the three
-// directions in one kernel and the first transverse stage of the three
-// directions in another.  Both give the same bits.
+// directions in one kernel, the first transverse stage of the three
+// directions in another, and the normal and the final fluxes of the three
+// directions in one launch each.  Both give the same bits.
 const int kCellStagesSplit[] = {kStFlatten, kStTraceX, kStTraceY, kStTraceZ, kStRiemX, kStRiemY, kStRiemZ,
                                 kStT1X, kStT1Y, kStT1Z, kStT2X, kStT2Y, kStT2Z, kStUpdate};
-const int kCellStagesFused[] = {kStTrace3, kStSpec3, kStRiemX, kStRiemY, kStRiemZ, kStT1All,
-                                kStT2X, kStT2Y, kStT2Z, kStUpdate};
+const int kCellStagesFused[] = {kStTrace3, kStSpec3, kStRiem3, kStT1All, kStT2All, kStUpdate};
 
 std::vector<int> cell_stages(const ctuppm_ctx* c) {
   if (c->fused) return std::vector<int>(std::begin(kCellStagesFused), std::end(kCellStagesFused));
@@ -1236,7 +1238,7 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
   const int nst = S->scheme == 1 ? 2 : 3;
   // face states: flattening and the three directions in one kernel (fused,
   // the default) or one kernel each
-  static const std::vector<int> fused = {kStRecon3, kStSpec3, kStRiemX, kStRiemY, kStRiemZ};
+  static const std::vector<int> fused = {kStRecon3, kStSpec3, kStRiem3};
   static const std::vector<int> split = {kStFlatten, kStReconX, kStReconY, kStReconZ, kStRiemX, kStRiemY, kStRiemZ};
   const std::vector<int>& cells = c->fused ? fused : split;
   int rc;
@@ -2548,6 +2550,13 @@ int ctuppm_stage_bytes(ctuppm_ctx* c, int pid, int stage, double* bytes) {
         tot += nq * W * cells1 / (nn[d] + 2) * (nn[d] + 6) + W * cells1 + 2 * nv * W * face(d);
         break;
       }
+      case kStRiem3: tot += nst * 3 * nv * W * (face(0) + face(1) + face(2)); break;
+      case kStT2All:
+        for (int a = 0; a < 3; ++a) {
+          const int b = (a + 1) % 3, cc = (a + 2) % 3;
+          tot += 3 * nv * W * fin(a) + nv * W * (half(b, cc) + half(cc, b));
+        }
+        break;
       case kStRiemX: case kStRiemY: case kStRiemZ: tot += nst * 3 * nv * W * face(stage - kStRiemX); break;
       case kStT1X: case kStT1Y: case kStT1Z: {
         const int a = stage - kStT1X, b = (a + 1) % 3, cc = (a + 2) % 3;

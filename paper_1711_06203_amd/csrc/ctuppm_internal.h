@@ -24,7 +24,9 @@ constexpr int kSlots = 64;   // signal-speed max accumulators per problem (sprea
 //   its work units can march through more planes than stage 1's (a block
 //   marching through consecutive planes finds the z stencils of the next
 //   plane in its caches)
-enum Region : int { kValid = 0, kGrown, kCells1, kFace0, kFace1, kFace2, kFin0, kFin1, kFin2, kCells1T, kNumRegions };
+//   kFin    x over [-1, n], y and z over [0, n]: covers kFin0, kFin1 and kFin2
+//   (the final fluxes of the three directions in one launch)
+enum Region : int { kValid = 0, kGrown, kCells1, kFace0, kFace1, kFace2, kFin0, kFin1, kFin2, kCells1T, kFin, kNumRegions };
 
 __host__ __device__ inline void region_of(int kind, const int n[3], int org[3], int ext[3]) {
   for (int d = 0; d < 3; ++d) {
@@ -34,6 +36,9 @@ __host__ __device__ inline void region_of(int kind, const int n[3], int org[3], 
       case kCells1: case kCells1T: org[d] = -1; ext[d] = n[d] + 2; break;
       case kFace0: case kFace1: case kFace2:
         if (d == kind - kFace0) { org[d] = 0; ext[d] = n[d] + 1; } else { org[d] = -1; ext[d] = n[d] + 2; }
+        break;
+      case kFin:
+        if (d == 0) { org[d] = -1; ext[d] = n[d] + 2; } else { org[d] = 0; ext[d] = n[d] + 1; }
         break;
       default:
         if (d == 0) { org[d] = -1; ext[d] = n[d] + 2; }
@@ -168,7 +173,8 @@ enum Stage : int {
   kStFill = 0, kStBcX, kStBcY, kStBcZ, kStC2P, kStCfl, kStC2POnly, kStDt, kStFlatten,
   kStTraceX, kStTraceY, kStTraceZ, kStRiemX, kStRiemY, kStRiemZ, kStT1X, kStT1Y, kStT1Z,
   kStT2X, kStT2Y, kStT2Z, kStUpdate, kStFlip,
-  kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kNumStages
+  kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kStRiem3, kStT2All,
+  kNumStages
 };
 
 // State array a stage reads (fill, boundaries, cons->prim, MOL stages) or
@@ -190,11 +196,14 @@ __host__ __device__ inline int stage_region(int stage) {
     case kStRiemX: case kStRiemY: return kCells1;  // whole rows / planes of stores
     case kStT1X: return kFace0;
     case kStT1Y: return kFace1;
-    case kStRiemZ: case kStT1Z: return kFace2;
+    case kStRiemZ: return kCells1;
+    case kStT1Z: return kFace2;
     case kStT2X: return kFin0;
     case kStT2Y: return kFin1;
     case kStT2Z: return kFin2;
     case kStUpdate: return kValid;
+    case kStRiem3: return kCells1;  // once per direction
+    case kStT2All: return kFin;     // once per direction
     default: return -1;
   }
 }

@@ -42,13 +42,17 @@ using CProb = __attribute__((address_space(4))) const ProbDev;
 CTU_DEV CProb* cprob(const ProbDev* P) { return (CProb*)P; }
 
 template <class F>
-CTU_DEV void for_each_chunk(int nchunks, F&& f) {
-  const int per = gridDim.x >> 3;
-  const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+CTU_DEV void for_each_chunk(int nchunks, int block, int blocks, F&& f) {
+  const int per = blocks >> 3;
+  const int xcd = block & 7, local = block >> 3;
   const int span = (nchunks + 7) >> 3;
   const int beg = xcd * span;
   const int end = beg + span < nchunks ? beg + span : nchunks;
   for (int c = beg + local; c < end; c += per) f(c);
+}
+template <class F>
+CTU_DEV void for_each_chunk(int nchunks, F&& f) {
+  for_each_chunk(nchunks, blockIdx.x, gridDim.x, f);
 }
 
 // Segment of launch item c (block-uniform: a scalar scan over the kernel
@@ -74,6 +78,20 @@ CTU_DEV void for_each_unit(const Segs& L, F&& f) {
   for_each_chunk(L.beg[L.n], [&](int c) {
     const int s = seg_of(L, c);
     unit_body((const March*)L.s[s].work, L.s[s].boxes, c - L.beg[s], f);
+  });
+}
+
+// Visit the march units of a launch once per direction: f(direction, unit, its
+// box).  A third of the grid (a multiple of 8 blocks) takes all units along
+// x, the next third y, the last z, so blocks start in the order of three
+// launches and each direction keeps the mapping of units to XCDs.
+template <class F>
+CTU_DEV void for_each_unit_dir(const Segs& L, F&& f) {
+  const int blocks = gridDim.x / 3, d = blockIdx.x / blocks;
+  for_each_chunk(L.beg[L.n], blockIdx.x - d * blocks, blocks, [&](int c) {
+    const int s = seg_of(L, c);
+    unit_body((const March*)L.s[s].work, L.s[s].boxes, c - L.beg[s],
+              [&](const March& M, const BoxRec& B) { f(d, M, B); });
   });
 }
 
@@ -794,37 +812,54 @@ CTU_DEV void wall_mirror(int side, double L[5], double R[5]) {
 // planes (y): the slot of face -1, which nothing reads, takes zeros instead
 // of leaving a partly written line in every row.
 template <int D, int RS>
-__global__ __launch_bounds__(kBlock) void k_riemann(const Segs L) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
-    CProb* P = cprob(B.P);
-    const Geo g(B.n, B.ns);
-    const gdbl* __restrict__ ql = g.ql(B.scr, D);
-    const gdbl* __restrict__ qr = g.qr(B.scr, D);
-    gdbl* __restrict__ fn = g.fn(B.scr, D);
-    march(D == 2 ? kFace2 : kCells1, B, M, [&](int i, int j, int k) {
-      const int o = g.h(i, j, k);
-      const int fa = D == 0 ? i : (D == 1 ? j : k);
-      if (fa < 0) {
-        for (int m = 0; m < g.nv; ++m) fn[m * g.hcomp + o] = 0.0;
-        return;
-      }
-      const int side = wall_side(B, D, fa);
-      double L[5], R[5], f[5];
+CTU_DEV void riemann_unit(const March& M, const BoxRec& B) {
+  CProb* P = cprob(B.P);
+  const Geo g(B.n, B.ns);
+  const gdbl* __restrict__ ql = g.ql(B.scr, D);
+  const gdbl* __restrict__ qr = g.qr(B.scr, D);
+  gdbl* __restrict__ fn = g.fn(B.scr, D);
+  march(kCells1, B, M, [&](int i, int j, int k) {
+    const int o = g.h(i, j, k);
+    const int fa = D == 0 ? i : (D == 1 ? j : k);
+    if (fa < 0) {
+      if (D == 2) return;  // a plane of its own: no line is partly written without it
+      for (int m = 0; m < g.nv; ++m) fn[m * g.hcomp + o] = 0.0;
+      return;
+    }
+    const int side = wall_side(B, D, fa);
+    double L[5], R[5], f[5];
 #pragma unroll
-      for (int m = 0; m < 5; ++m) {
-        L[m] = ql[m * g.hcomp + o];
-        R[m] = qr[m * g.hcomp + o];
-      }
-      wall_mirror(side, L, R);
-      Wave W;
-      rflux<RS>(L, R, P, f, W);
-      store_flux<D>(fn, g.hcomp, o, f);
-      for (int is = 0; is < g.ns; ++is) {
-        const int mo = (kNV + is) * g.hcomp + o;
-        const double xl = ql[mo], xr = qr[mo];
-        fn[mo] = species_flux(W, side == 1 ? xr : xl, side == 2 ? xl : xr);
-      }
-    });
+    for (int m = 0; m < 5; ++m) {
+      L[m] = ql[m * g.hcomp + o];
+      R[m] = qr[m * g.hcomp + o];
+    }
+    wall_mirror(side, L, R);
+    Wave W;
+    rflux<RS>(L, R, P, f, W);
+    store_flux<D>(fn, g.hcomp, o, f);
+    for (int is = 0; is < g.ns; ++is) {
+      const int mo = (kNV + is) * g.hcomp + o;
+      const double xl = ql[mo], xr = qr[mo];
+      fn[mo] = species_flux(W, side == 1 ? xr : xl, side == 2 ? xl : xr);
+    }
+  });
+}
+
+template <int D, int RS>
+__global__ __launch_bounds__(kBlock) void k_riemann(const Segs L) {
+  for_each_unit(L, [&](const March& M, const BoxRec& B) { riemann_unit<D, RS>(M, B); });
+}
+
+// The three directions in one launch: bound by memory on a large level (5.3
+// TB/s, the rate of a copy), by the launch itself on a small one.  A 32^3 box
+// takes 8.0 us for the three instead of 20.1, a 256^3 level 1.223 ms instead
+// of 1.250.
+template <int RS>
+__global__ __launch_bounds__(kBlock) void k_riemann3(const Segs L) {
+  for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
+    if (d == 0) riemann_unit<0, RS>(M, B);
+    else if (d == 1) riemann_unit<1, RS>(M, B);
+    else riemann_unit<2, RS>(M, B);
   });
 }
 
@@ -1042,18 +1077,37 @@ CTU_DEV void final_flux(const BoxRec& B, const Geo& g, CProb* P, int o, int fa, 
 
 // Stage 2 along A over faces 0..n (cells 0..n-1 across): final fluxes; the
 // threads cover whole rows (x over -1..n) and store zeros off the faces.
+// REGION: kFin0 + A, or kFin (one work list for the three directions, with a
+// row and a plane more than the faces along x, y or z take).
+template <int A, int RS, int REGION>
+CTU_DEV void trans2_unit(const March& M, const BoxRec& B) {
+  CProb* P = cprob(B.P);
+  const Geo g(B.n, B.ns);
+  gdbl* __restrict__ ff = g.ff(B.scr, A);
+  int fb = 0;
+  const int ilast = A == 0 ? B.n[0] : B.n[0] - 1;  // last x index holding a face
+  march(REGION, B, M, [&](int i, int j, int k) {
+    if (REGION == kFin && ((A != 1 && j >= B.n[1]) || (A != 2 && k >= B.n[2]))) return;
+    final_flux<A, RS>(B, g, P, g.h(i, j, k), A == 0 ? i : (A == 1 ? j : k), i >= 0 && i <= ilast, ff, fb);
+  });
+  count(&B.P->cnt[3], (unsigned long long)fb);
+}
+
 template <int A, int RS>
 __global__ __launch_bounds__(kBlock) void k_trans2(const Segs L) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
-    CProb* P = cprob(B.P);
-    const Geo g(B.n, B.ns);
-    gdbl* __restrict__ ff = g.ff(B.scr, A);
-    int fb = 0;
-    const int ilast = A == 0 ? B.n[0] : B.n[0] - 1;  // last x index holding a face
-    march(kFin0 + A, B, M, [&](int i, int j, int k) {
-      final_flux<A, RS>(B, g, P, g.h(i, j, k), A == 0 ? i : (A == 1 ? j : k), i >= 0 && i <= ilast, ff, fb);
-    });
-    count(&B.P->cnt[3], (unsigned long long)fb);
+  for_each_unit(L, [&](const March& M, const BoxRec& B) { trans2_unit<A, RS, kFin0 + A>(M, B); });
+}
+
+// The three directions in one launch.  A 32^3 box takes 11 us instead of 26
+// (three launches that leave most CUs idle), a 256^3 level 2.31 ms either
+// way.  With the units of all directions dealt to the XCDs as one list (a
+// direction per XCD at any time) it took 2.49 ms.
+template <int RS>
+__global__ __launch_bounds__(kBlock) void k_trans2_3(const Segs L) {
+  for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
+    if (d == 0) trans2_unit<0, RS, kFin>(M, B);
+    else if (d == 1) trans2_unit<1, RS, kFin>(M, B);
+    else trans2_unit<2, RS, kFin>(M, B);
   });
 }
 
@@ -1562,7 +1616,8 @@ const char* stage_name(int s) {
       "fill", "bc_x", "bc_y", "bc_z", "cons2prim_cfl", "cfl", "cons2prim", "dt", "flatten",
       "trace_x", "trace_y", "trace_z", "riemann_x", "riemann_y", "riemann_z",
       "trans1_x", "trans1_y", "trans1_z", "trans2_x", "trans2_y", "trans2_z", "update", "flip",
-      "recon_x", "recon_y", "recon_z", "mol_update", "trace_xyz", "trans1_xyz", "recon_xyz", "species_xyz"};
+      "recon_x", "recon_y", "recon_z", "mol_update", "trace_xyz", "trans1_xyz", "recon_xyz", "species_xyz",
+      "riemann_xyz", "trans2_xyz"};
   return (s >= 0 && s < kNumStages) ? names[s] : "?";
 }
 
@@ -1631,6 +1686,7 @@ hipError_t launch_stage(int stage, const Launch& L) {
         else k_trans1_all<0, false><<<grid, block, 0, s>>>(G);
       }
       break;
+#define CTU_RS3(K) (L.rs ? K<1><<<grid, block, 0, s>>>(G) : K<0><<<grid, block, 0, s>>>(G))
 #define CTU_RS(K, D) (L.rs ? K<D, 1><<<grid, block, 0, s>>>(G) : K<D, 0><<<grid, block, 0, s>>>(G))
     case kStRiemX: CTU_RS(k_riemann, 0); break;
     case kStRiemY: CTU_RS(k_riemann, 1); break;
@@ -1641,6 +1697,9 @@ hipError_t launch_stage(int stage, const Launch& L) {
     case kStT2X: CTU_RS(k_trans2, 0); break;
     case kStT2Y: CTU_RS(k_trans2, 1); break;
     case kStT2Z: CTU_RS(k_trans2, 2); break;
+    case kStRiem3: CTU_RS3(k_riemann3); break;
+    case kStT2All: CTU_RS3(k_trans2_3); break;
+#undef CTU_RS3
 #undef CTU_RS
     case kStUpdate: k_update<<<grid, block, 0, s>>>(G); break;
     default: return hipErrorInvalidValue;
