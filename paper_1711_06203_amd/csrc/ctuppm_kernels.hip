@@ -796,14 +796,17 @@ CTU_DEV int wall_side(const BoxRec& B, int d, int fa) {
   return 0;
 }
 
-// Permuted primitive states (slot 1 the normal velocity).
+// Permuted primitive states (slot 1 the normal velocity).  A branch, not
+// selects: away from the walls a wave skips it (the selects were 20
+// instructions of every flux).
 CTU_DEV void wall_mirror(int side, double L[5], double R[5]) {
-  const bool lo = side == 1, hi = side == 2;
+  if (side == 0) return;
+  const bool lo = side == 1;
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     const double l = L[m], r = R[m];
     L[m] = lo ? (m == 1 ? -r : r) : l;
-    R[m] = hi ? (m == 1 ? -l : l) : r;
+    R[m] = lo ? r : (m == 1 ? -l : l);
   }
 }
 
@@ -883,13 +886,14 @@ CTU_DEV int to_prim_or_keep(const double U[5], const double s0[5], double gm1, d
   const double un = U[1 + A] / rho, ut1 = U[1 + (A + 1) % 3] / rho, ut2 = U[1 + (A + 2) % 3] / rho;
   const double ke = 0.5 * rho * ((un * un + ut1 * ut1) + ut2 * ut2);
   const double p = gm1 * (U[4] - ke);
-  if (rho < sd || p < sp) {
-#pragma unroll
-    for (int m = 0; m < 5; ++m) s[m] = s0[m];
-    return 1;
-  }
   s[0] = rho; s[1] = un; s[2] = ut1; s[3] = ut2; s[4] = p;
-  return 0;
+  const bool keep = rho < sd || p < sp;
+  // a branch a wave skips when none of its states failed, not selects
+  if (__builtin_amdgcn_ballot_w64(keep) != 0) {
+#pragma unroll
+    for (int m = 0; m < 5; ++m) s[m] = keep ? s0[m] : s[m];
+  }
+  return keep;
 }
 
 // Stage 1 at one face along A: the face states corrected by dt/(3 dx_B)

@@ -21,6 +21,10 @@ namespace ctu {
 CTU_DEV double dmin(double a, double b) { return a < b ? a : b; }
 CTU_DEV double dmax(double a, double b) { return a > b ? a : b; }
 
+// True when `c` holds on any lane of the wave: guards work that is rarely
+// needed, so a wave skips it instead of computing and discarding it.
+CTU_DEV bool any_lane(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
+
 // Monotonised-central slope of the middle of three cell values.
 CTU_DEV double mc_slope(double am, double a0, double ap) {
   const double dm = a0 - am, dp = ap - a0, dc = 0.5 * (ap - am);
@@ -179,27 +183,33 @@ CTU_DEV double avg_left(const Parab& p, double sig) {
 // speeds; reference from the u-c family).
 CTU_DEV void trace_up(const Parab par[5], double rho, double un, double c, double dtdx, double up[5]) {
   const double lm = un - c, l0 = un, lp = un + c;
-  const double sm = fabs(lm) * dtdx, s0 = fabs(l0) * dtdx, sp = fabs(lp) * dtdx;
   const double csq = c * c;
-  double Im[5], I0[5], ref[5];
+  const double sp = fabs(lp) * dtdx;
+  double ref[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
-    Im[m] = lm > 0.0 ? avg_right(par[m], sm) : par[m].aR;
-    I0[m] = l0 > 0.0 ? avg_right(par[m], s0) : par[m].aR;
     ref[m] = lp > 0.0 ? avg_right(par[m], sp) : par[m].aR;
+    up[m] = ref[m];
   }
-  const double bm = -(rho / (2.0 * c)) * (ref[1] - Im[1]) + (ref[4] - Im[4]) / (2.0 * csq);
-  const double b0 = (ref[0] - I0[0]) - (ref[4] - I0[4]) / csq;
-  const double bt1 = ref[2] - I0[2];
-  const double bt2 = ref[3] - I0[3];
-#pragma unroll
-  for (int m = 0; m < 5; ++m) up[m] = ref[m];
-  if (lm > 0.0) {
-    up[0] = up[0] - bm;
-    up[1] = up[1] - bm * (-(c / rho));
-    up[4] = up[4] - bm * csq;
+  // the families that do not move towards the face contribute nothing: a
+  // wave skips the u-c family in subsonic flow (three divisions of four; the
+  // merged tracing of a 32^3 box 15.8 -> 14.6 us, of 256^3 1.98 -> 1.96 ms)
+  if (any_lane(lm > 0.0)) {
+    const double sm = fabs(lm) * dtdx;
+    const double I1 = lm > 0.0 ? avg_right(par[1], sm) : par[1].aR;
+    const double I4 = lm > 0.0 ? avg_right(par[4], sm) : par[4].aR;
+    const double bm = -(rho / (2.0 * c)) * (ref[1] - I1) + (ref[4] - I4) / (2.0 * csq);
+    if (lm > 0.0) {
+      up[0] = up[0] - bm;
+      up[1] = up[1] - bm * (-(c / rho));
+      up[4] = up[4] - bm * csq;
+    }
   }
   if (l0 > 0.0) {
+    const double s0 = fabs(l0) * dtdx;
+    const double b0 = (ref[0] - avg_right(par[0], s0)) - (ref[4] - avg_right(par[4], s0)) / csq;
+    const double bt1 = ref[2] - avg_right(par[2], s0);
+    const double bt2 = ref[3] - avg_right(par[3], s0);
     up[0] = up[0] - b0;
     up[2] = up[2] - bt1;
     up[3] = up[3] - bt2;
@@ -208,27 +218,30 @@ CTU_DEV void trace_up(const Parab par[5], double rho, double un, double c, doubl
 
 CTU_DEV void trace_dn(const Parab par[5], double rho, double un, double c, double dtdx, double dn[5]) {
   const double lm = un - c, l0 = un, lp = un + c;
-  const double sm = fabs(lm) * dtdx, s0 = fabs(l0) * dtdx, sp = fabs(lp) * dtdx;
   const double csq = c * c;
-  double Ip[5], I0[5], ref[5];
+  const double sm = fabs(lm) * dtdx;
+  double ref[5];
 #pragma unroll
   for (int m = 0; m < 5; ++m) {
     ref[m] = lm < 0.0 ? avg_left(par[m], sm) : par[m].aL;
-    I0[m] = l0 < 0.0 ? avg_left(par[m], s0) : par[m].aL;
-    Ip[m] = lp < 0.0 ? avg_left(par[m], sp) : par[m].aL;
+    dn[m] = ref[m];
   }
-  const double bp = (rho / (2.0 * c)) * (ref[1] - Ip[1]) + (ref[4] - Ip[4]) / (2.0 * csq);
-  const double b0 = (ref[0] - I0[0]) - (ref[4] - I0[4]) / csq;
-  const double bt1 = ref[2] - I0[2];
-  const double bt2 = ref[3] - I0[3];
-#pragma unroll
-  for (int m = 0; m < 5; ++m) dn[m] = ref[m];
-  if (lp < 0.0) {
-    dn[0] = dn[0] - bp;
-    dn[1] = dn[1] - bp * (c / rho);
-    dn[4] = dn[4] - bp * csq;
+  if (any_lane(lp < 0.0)) {
+    const double sp = fabs(lp) * dtdx;
+    const double I1 = lp < 0.0 ? avg_left(par[1], sp) : par[1].aL;
+    const double I4 = lp < 0.0 ? avg_left(par[4], sp) : par[4].aL;
+    const double bp = (rho / (2.0 * c)) * (ref[1] - I1) + (ref[4] - I4) / (2.0 * csq);
+    if (lp < 0.0) {
+      dn[0] = dn[0] - bp;
+      dn[1] = dn[1] - bp * (c / rho);
+      dn[4] = dn[4] - bp * csq;
+    }
   }
   if (l0 < 0.0) {
+    const double s0 = fabs(l0) * dtdx;
+    const double b0 = (ref[0] - avg_left(par[0], s0)) - (ref[4] - avg_left(par[4], s0)) / csq;
+    const double bt1 = ref[2] - avg_left(par[2], s0);
+    const double bt2 = ref[3] - avg_left(par[3], s0);
     dn[0] = dn[0] - b0;
     dn[2] = dn[2] - bt1;
     dn[3] = dn[3] - bt2;
