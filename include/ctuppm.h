@@ -416,7 +416,8 @@ int ctuppm_set_wave_boxes(ctuppm_ctx* ctx, int boxes);
  * stage "species_xyz", launched only for problems with species),
  * the first transverse stage of the three directions (CTU) in one kernel
  * that reads each normal flux array once, and the normal and the final fluxes
- * of the three directions in one launch each; 2, as 1 with the species traced
+ * of the three directions in one launch each (the method of lines without
+ * species takes its normal fluxes inside the update instead); 2, as 1 with the species traced
  * inside the merged kernels (no species stage); off (0), a flattening kernel
  * and one kernel per direction.  Results are the same bits in every mode
  * (each face takes the same arithmetic); captured graphs are dropped.

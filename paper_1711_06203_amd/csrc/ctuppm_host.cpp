@@ -109,6 +109,7 @@ struct Problem {
   bool filled[2] = {false, false};   // ghosts of the level's current state filled since it last changed
   bool dt_ready = false;             // dt computed since the last advance
   bool averaged = false;             // fine level averaged down in this coarse step
+  int scratch_rf = -1;               // scratch layout (record form) the last advance left its arrays in, -1 none
   void state_changed() {
     filled[0] = filled[1] = false;
     dt_ready = false;
@@ -1210,6 +1211,25 @@ std::vector<std::pair<int, int>> box_groups(const ctuppm_ctx* c, const StepSet* 
   return g;
 }
 
+// Recompute a stage of the box that last used `box`'s scratch in `form`, from
+// the arrays that box left there: for stage dumps of arrays a fused kernel
+// keeps out of memory.  Does nothing when the last advance used another layout.
+int recompute_stage(ctuppm_ctx* c, Problem* P, int level, int box, int form, int stage) {
+  const int rf = rec_form(form);
+  if (P->scratch_rf != rf || ensure_tables(c, P) != CTUPPM_OK) return CTUPPM_OK;
+  const int nb = int(P->lev[level].boxes.size());
+  int b = box;
+  if (form == CTUPPM_FORM_PER_BOX) b = nb - 1;
+  if (form == CTUPPM_FORM_WAVES) b += (nb - 1 - box) / c->wave_boxes * c->wave_boxes;
+  const LevelTables& T = P->lt[level];
+  const std::vector<int>& pre = T.upre[2][stage_region(stage)];
+  SegRun R{c, c->stream, stage, false, false, StageArgs()};
+  R.A.rs = P->prm.riemann;
+  const int rc = R.add(T.recs[rf], T.units[2][stage_region(stage)] + pre[b], nullptr, level_rec(P, level),
+                       pre[b + 1] - pre[b]);
+  return rc ? rc : R.flush();
+}
+
 // Ghost fill of the state array `arr` of every box of a set: same-level
 // copies, then the physical boundaries x, y, z (box by box in the per-box form).
 int fill_arr(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int arr) {
@@ -1237,10 +1257,15 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
   const bool per_box = S->form == CTUPPM_FORM_PER_BOX;
   const int nst = S->scheme == 1 ? 2 : 3;
   // face states: flattening and the three directions in one kernel (fused,
-  // the default) or one kernel each
-  static const std::vector<int> fused = {kStRecon3, kStSpec3, kStRiem3};
+  // the default) or one kernel each.  Without species the fused form leaves
+  // the normal fluxes to the update; with them the update would read every
+  // species' z states twice from memory (two planes of 18 components do not
+  // stay in an XCD's L2: KH 128^3 with 13 species 2.11 ms a step against 2.01
+  // for the two kernels; without species 1.10 against 1.73 ms at 160^3)
+  const bool fluxup = c->fused && !S->species;
+  static const std::vector<int> fused_up = {kStRecon3}, fused = {kStRecon3, kStSpec3, kStRiem3};
   static const std::vector<int> split = {kStFlatten, kStReconX, kStReconY, kStReconZ, kStRiemX, kStRiemY, kStRiemZ};
-  const std::vector<int>& cells = c->fused ? fused : split;
+  const std::vector<int>& cells = fluxup ? fused_up : c->fused ? fused : split;
   int rc;
   for (int r = 0; r < nst; ++r) {
     const int arr = r == 0 ? kArrCur : (r == 1 ? kArrW0 : kArrW1);
@@ -1269,7 +1294,7 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
         return rc;
       for (int st : cells)
         if ((rc = run_range(c, S, s, st, g.first, g.second, timed))) return rc;
-      if ((rc = run_range(c, S, s, kStMolUpdate, g.first, g.second, timed, U))) return rc;
+      if ((rc = run_range(c, S, s, fluxup ? kStMolFlux : kStMolUpdate, g.first, g.second, timed, U))) return rc;
     }
   }
   return run_probs(c, S, s, true, guard);
@@ -1575,6 +1600,7 @@ int step_set(ctuppm_ctx* c, const std::vector<int>& v, int form, int guard) {
     P->cur ^= 1;
     P->steps += 1;
     if (guard) P->guarded = true;  // the mirror holds only if no step is rejected
+    P->scratch_rf = rec_form(S->form);
     P->state_changed();
   }
   return CTUPPM_OK;
@@ -1850,6 +1876,7 @@ int ctuppm_bind_workspace(ctuppm_ctx* c, int pid, void* ws, size_t bytes) {
       if (rc) return rc;
     }
   }
+  P->scratch_rf = -1;
   P->ws = ws;
   P->ws_bytes = bytes;
   P->dP = (ProbDev*)ws;
@@ -2394,6 +2421,11 @@ int ctuppm_debug_stage(ctuppm_ctx* c, int pid, int level, int box, int array, in
     return fail(c, CTUPPM_ENOMEM, "problem %d: array %d of box %d in form %d ends at byte %zu of a %zu-byte workspace",
                 pid, array, box, form, end, P->ws_bytes);
   if (!out) return CTUPPM_OK;
+  // the method of lines without species keeps its normal fluxes out of memory
+  if (array >= 8 && array <= 10 && P->prm.scheme != CTUPPM_SCHEME_CTU && ns == 0) {
+    const int rc = recompute_stage(c, P, level, box, form, kStRiem3);
+    if (rc) return rc;
+  }
   const double* src = (const double*)((const char*)P->ws + off) + first;
   if (array == 0) {
     HIPCHK(c, hipMemcpyAsync(out, src, size_t(count) * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
@@ -2538,6 +2570,11 @@ int ctuppm_stage_bytes(ctuppm_ctx* c, int pid, int stage, double* bytes) {
         tot += nst * ((nq - 1) * W * cells1 / (nn[d] + 2) * (nn[d] + 6) + W * cells1 + 2 * nv * W * face(d));
         break;
       }
+      case kStMolFlux:
+        // per stage: the face states, the stage input and the output; the
+        // combination stages also read the current state
+        tot += nst * (2 * nv * W * (fin(0) + fin(1) + fin(2)) + 2 * nv * W * valid) + (nst - 1) * nv * W * valid;
+        break;
       case kStMolUpdate:
         // per stage: the stage input, three flux arrays and the output; the
         // combination stages also read the current state

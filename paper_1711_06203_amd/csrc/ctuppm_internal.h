@@ -173,7 +173,7 @@ enum Stage : int {
   kStFill = 0, kStBcX, kStBcY, kStBcZ, kStC2P, kStCfl, kStC2POnly, kStDt, kStFlatten,
   kStTraceX, kStTraceY, kStTraceZ, kStRiemX, kStRiemY, kStRiemZ, kStT1X, kStT1Y, kStT1Z,
   kStT2X, kStT2Y, kStT2Z, kStUpdate, kStFlip,
-  kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kStRiem3, kStT2All,
+  kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kStRiem3, kStT2All, kStMolFlux,
   kNumStages
 };
 
@@ -192,7 +192,7 @@ __host__ __device__ inline int stage_region(int stage) {
     case kStTrace3: case kStRecon3: case kStSpec3: return kCells1T;
     case kStTraceX: case kStTraceY: case kStTraceZ: return kCells1;
     case kStReconX: case kStReconY: case kStReconZ: return kCells1;
-    case kStMolUpdate: return kValid;
+    case kStMolUpdate: case kStMolFlux: return kValid;
     case kStRiemX: case kStRiemY: return kCells1;  // whole rows / planes of stores
     case kStT1X: return kFace0;
     case kStT1Y: return kFace1;

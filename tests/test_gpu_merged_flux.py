@@ -72,3 +72,27 @@ def test_more_problems_than_one_launch_holds(ctx):
         ref, _, _ = oracle.run_problem(p, 2)
         assert np.array_equal(s.state(), ref), p.n
         s.close()
+
+
+@pytest.mark.parametrize("form,box", [("batched", 1), ("graph", 0), ("per_box", 2), ("waves", 2)])
+def test_mol_dump_of_fluxes_kept_out_of_memory(ctx, form, box):
+    """Without species the method of lines solves its normal fluxes inside the
+    update; a stage dump still returns them, for the box that used the scratch last."""
+    from paper_1711_06203_amd import ctuppm
+    prob = W.rayleigh_taylor(n=(16, 12, 21), seed=5, boxes=W.regular_boxes((16, 12, 21), (16, 12, 7)))
+    prob.scheme, prob.riemann = 1, 1
+    ctx.set_wave_boxes(2)
+    got = {}
+    for fused in (1, 0):
+        ctx.set_fused(fused)
+        s = ctuppm.Solver(ctx, prob, form=form)
+        s.step(2)
+        before = s.counters()
+        got[fused] = [s.stage_array(box, f"fn{d}", form=form) for d in range(3)]
+        assert np.array_equal(before, s.counters())
+        s.close()
+    ctx.set_wave_boxes(64)
+    for d in range(3):
+        face = [slice(None)] * 4
+        face[3 - d] = slice(1, None)  # faces 0..n; the slot below holds none
+        assert np.array_equal(got[1][d][tuple(face)], got[0][d][tuple(face)])
