@@ -54,6 +54,7 @@ struct LevelTables {
   FillTag* ftags = nullptr;
   Chunk* fch = nullptr;
   std::vector<int> fpre;
+  long long fcells = 0;  // ghost cells the copy tags fill
   BcTag* btags[3] = {};
   Chunk* bch[3] = {};
   std::vector<int> bpre[3];
@@ -130,6 +131,8 @@ struct StepSet {
   int limiter = 0;  // likewise (reconstruction variant: 0 CW84, 1 CS, 2 CW84 + steepening)
   int species = 0;  // 1 when a problem of the set carries passive species
   int nboxes = 0;
+  int copies = 0;   // ghost fill and conversion in one launch: fin, and every ghost cell is a copy of a valid cell
+  int fin = 0;      // dt and the commit by the last blocks of the conversion and the update
   int zvar = 0;     // work-unit variant of its launches (LevelTables)
   hipGraph_t graph[2] = {nullptr, nullptr};  // captured step, unguarded / guarded
   hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -343,6 +346,13 @@ void march_region(std::vector<March>& out, int box, const int org[3], const int 
   }
 }
 
+// Sets of at most this many update units are bound by their launches, and take
+// fewer: dt and the commit in the last blocks of the conversion and the update
+// (a 32^3 box: 5 us less each), and, where every ghost cell is a copy, ghost
+// fill and conversion together (KH 100x77x61, 1835 units: 72 -> 53 us; serving
+// mix of ten problems, 19000 units: 154 -> 165 us).
+constexpr int kFinUnits = 2048;
+
 constexpr int kMinUnitsPerCu = 8;  // deeper work units only while a level keeps this many per CU
 
 // Most march units one box region can have under any tuning (one row per
@@ -444,12 +454,14 @@ struct StageArgs {
   int lim = 0;
   int sp = 0;
   int mol = 0;
+  int fin = 0;
+  int guard = 0;
   int spstage = 0;
 };
 
 // Launch one stage over a segment list with optional timing.
 int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool persistent, bool timed,
-                const StageArgs& A) {
+                const StageArgs& A, const Segs* tags = nullptr) {
   if (G.n <= 0 || G.beg[G.n] <= 0) return CTUPPM_OK;
   Launch L{};
   L.segs = G;
@@ -466,6 +478,8 @@ int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool per
   L.lim = A.lim;
   L.sp = A.sp;
   L.mol = A.mol;
+  L.fin = A.fin;
+  L.guard = A.guard;
   L.spstage = A.spstage;
   hipEvent_t a = nullptr, b = nullptr;
   if (timed) {
@@ -474,7 +488,8 @@ int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool per
     if (!a || !b) return fail(c, CTUPPM_EHIP, "hipEventCreate failed");
     HIPCHK(c, hipEventRecord(a, s));
   }
-  hipError_t e = launch_stage(stage, L);
+  hipError_t e = tags ? launch_fill_c2p(L, *tags, grid_for(c, tags->beg[tags->n], false), stage == kStFillC2P)
+                      : launch_stage(stage, L);
   if (e != hipSuccess) return fail(c, CTUPPM_EHIP, "launch of %s: %s", stage_name(stage), hipGetErrorString(e));
   if (timed) {
     HIPCHK(c, hipEventRecord(b, s));
@@ -573,6 +588,33 @@ int run_probs(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool flip, int guard) {
       if (rc) return rc;
     }
     G.s[G.n++].P = level_rec(P, S->level);
+  }
+  return go();
+}
+
+// Ghost fill and conversion of every box of a set whose ghost cells are all
+// copies (with the CFL reduction, and dt if the set takes it there).
+int run_fill_c2p(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool cfl, bool timed, const StageArgs& A) {
+  const int rf = rec_form(S->form);
+  Segs G{}, T{};
+  auto go = [&]() -> int {
+    const int rc = launch_segs(c, s, cfl ? kStFillC2P : kStFillC2POnly, G, S->form != CTUPPM_FORM_PER_BOX, timed, A, &T);
+    G = Segs{};
+    T = Segs{};
+    return rc;
+  };
+  for (Problem* P : S->probs) {
+    if (G.n == kMaxSeg) {
+      const int rc = go();
+      if (rc) return rc;
+    }
+    const LevelTables& L = P->lt[S->level];
+    ProbDev* rec = level_rec(P, S->level);
+    G.s[G.n] = Seg{L.recs[rf], L.units[S->zvar][kValid], nullptr, rec};
+    G.beg[G.n + 1] = G.beg[G.n] + L.upre[S->zvar][kValid].back();
+    T.s[G.n] = Seg{L.recs[rf], L.fch, L.ftags, rec};
+    T.beg[G.n + 1] = T.beg[G.n] + L.fpre.back();
+    T.n = G.n += 1;
   }
   return go();
 }
@@ -1068,6 +1110,8 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
     std::vector<FillTag> ft;
     std::vector<Chunk> fch;
     fill_tags(P, l, ft, fch, T.fpre);
+    T.fcells = 0;
+    for (const auto& t : ft) T.fcells += (long long)t.ext[0] * t.ext[1] * t.ext[2];
     T.ftags = K.put(ft);
     T.fch = K.put(fch);
     for (int d = 0; d < 3; ++d) {
@@ -1182,6 +1226,19 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   long long deep = 0;
   for (Problem* P : S->probs) deep += P->lt[level].upre[0][kCells1T].back();
   S->zvar = S->form == CTUPPM_FORM_PER_BOX ? 1 : (deep < (long long)kMinUnitsPerCu * c->num_cus ? 2 : 0);
+  long long upd = 0, ghosts = 0;
+  for (Problem* P : S->probs) {
+    const LevelTables& T = P->lt[level];
+    upd += T.upre[S->zvar][kValid].back();
+    ghosts -= T.fcells;
+    for (const auto& b : P->lev[level].boxes) {
+      const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
+      ghosts += grown_cells(n) - box_vol(b);
+    }
+  }
+  S->fin = upd <= kFinUnits && (S->form != CTUPPM_FORM_PER_BOX || S->nboxes == 1) && S->form != CTUPPM_FORM_WAVES &&
+           S->probs[0]->nlevels == 1;
+  S->copies = S->fin && ghosts == 0;
   *out = S.get();
   c->sets[key] = std::move(S);
   return CTUPPM_OK;
@@ -1269,19 +1326,31 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
   int rc;
   for (int r = 0; r < nst; ++r) {
     const int arr = r == 0 ? kArrCur : (r == 1 ? kArrW0 : kArrW1);
-    if ((rc = fill_arr(c, S, s, timed, arr))) return rc;
     StageArgs A;
     A.arr = arr;
+    A.fin = S->fin;
+    const bool own = S->form == CTUPPM_FORM_BATCHED || S->form == kFormStatic || S->nboxes == 1;
+    const bool merged = c->fused && S->copies && own;
+    if (merged) {
+      if ((rc = run_fill_c2p(c, S, s, r == 0, timed, A))) return rc;
+    } else if ((rc = fill_arr(c, S, s, timed, arr))) {
+      return rc;
+    }
     if (r == 0) {
-      if (per_box) {
+      if (merged) {
+      } else if (own) {
+        if ((rc = run_all(c, S, s, kStC2P, timed, A))) return rc;
+      } else if (per_box) {
         for (int b = 0; b < S->nboxes; ++b)
           if ((rc = run_range(c, S, s, kStCfl, b, b + 1, timed, A))) return rc;
-      } else if ((rc = run_all(c, S, s, S->form == CTUPPM_FORM_WAVES ? kStCfl : kStC2P, timed, A))) {
+      } else if ((rc = run_all(c, S, s, kStCfl, timed, A))) {
         return rc;
       }
-      if ((rc = run_probs(c, S, s, false, 0))) return rc;
+      if (!S->fin && (rc = run_probs(c, S, s, false, 0))) return rc;
     }
     StageArgs U;
+    U.fin = S->fin && r == nst - 1;
+    U.guard = guard;
     U.arr = arr;
     U.out = r == nst - 1 ? kArrNext : (r == 0 ? kArrW0 : kArrW1);
     U.comb = r > 0;
@@ -1289,15 +1358,14 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
     U.last = r == nst - 1;
     for (const auto& g : box_groups(c, S)) {
       // batched: the first stage's primitives came with the CFL pass
-      if ((per_box || S->form == CTUPPM_FORM_WAVES || r > 0) &&
-          (rc = run_range(c, S, s, kStC2POnly, g.first, g.second, timed, A)))
+      if (!merged && (!own || r > 0) && (rc = run_range(c, S, s, kStC2POnly, g.first, g.second, timed, A)))
         return rc;
       for (int st : cells)
         if ((rc = run_range(c, S, s, st, g.first, g.second, timed))) return rc;
       if ((rc = run_range(c, S, s, fluxup ? kStMolFlux : kStMolUpdate, g.first, g.second, timed, U))) return rc;
     }
   }
-  return run_probs(c, S, s, true, guard);
+  return S->fin ? CTUPPM_OK : run_probs(c, S, s, true, guard);
 }
 
 // Fork the two side streams off s (event slot k), and join them back.
@@ -1342,25 +1410,33 @@ int enqueue_step_branched(ctuppm_ctx* c, StepSet* S, hipStream_t s, int guard) {
 // Enqueue one step of a set on stream s.
 int enqueue_step(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard) {
   if (S->scheme != 0) return enqueue_mol(c, S, s, timed, guard);
-  const bool per_box = S->form == CTUPPM_FORM_PER_BOX;
-  const bool waves = S->form == CTUPPM_FORM_WAVES;
+  // every box its own scratch: the conversion's pass over the level also
+  // reduces the signal speed, and fills the ghost cells where all are copies.
+  // The other forms convert a box or a wave into its shared scratch right
+  // before its stages, so only the CFL pass runs over all boxes first.
+  const bool own = S->form == CTUPPM_FORM_BATCHED || S->form == kFormStatic || S->nboxes == 1;
+  StageArgs A;
+  A.fin = S->fin;
+  A.guard = guard;
   int rc;
-  if ((rc = fill_arr(c, S, s, timed, kArrCur))) return rc;
-  if (per_box) {
-    for (int b = 0; b < S->nboxes; ++b)
-      if ((rc = run_range(c, S, s, kStCfl, b, b + 1, timed))) return rc;
-  } else if ((rc = run_all(c, S, s, waves ? kStCfl : kStC2P, timed))) {
-    // the waves form converts each wave into its shared scratch right before
-    // the wave's stages, so only the CFL pass runs over all boxes here
-    return rc;
+  if (own && c->fused && S->copies) {
+    if ((rc = run_fill_c2p(c, S, s, true, timed, A))) return rc;
+  } else {
+    if ((rc = fill_arr(c, S, s, timed, kArrCur))) return rc;
+    if (own) {
+      if ((rc = run_all(c, S, s, kStC2P, timed, A))) return rc;
+    } else {
+      for (int b = 0; b < S->nboxes; b += S->form == CTUPPM_FORM_PER_BOX ? 1 : S->nboxes)
+        if ((rc = run_range(c, S, s, kStCfl, b, S->form == CTUPPM_FORM_PER_BOX ? b + 1 : S->nboxes, timed))) return rc;
+    }
   }
-  if ((rc = run_probs(c, S, s, false, 0))) return rc;
+  if (!S->fin && (rc = run_probs(c, S, s, false, 0))) return rc;
   for (const auto& g : box_groups(c, S)) {
-    if ((per_box || waves) && (rc = run_range(c, S, s, kStC2POnly, g.first, g.second, timed))) return rc;
+    if (!own && (rc = run_range(c, S, s, kStC2POnly, g.first, g.second, timed))) return rc;
     for (int st : cell_stages(c))
-      if ((rc = run_range(c, S, s, st, g.first, g.second, timed))) return rc;
+      if ((rc = run_range(c, S, s, st, g.first, g.second, timed, st == kStUpdate ? A : StageArgs()))) return rc;
   }
-  return run_probs(c, S, s, true, guard);
+  return S->fin ? CTUPPM_OK : run_probs(c, S, s, true, guard);
 }
 
 // ------------------------------------------------------------------ two levels
@@ -2560,6 +2636,11 @@ int ctuppm_stage_bytes(ctuppm_ctx* c, int pid, int stage, double* bytes) {
     auto half = [&](int a, int b) { return face(a) / (nn[b] + 2) * nn[b]; };         // F^{a|b} region
     switch (stage) {
       case kStFill: tot += nst * 2 * nv * W * (grown - valid); break;
+      case kStFillC2P: case kStFillC2POnly:
+        // the valid cells read, the ghost cells read from their sources and
+        // stored, the primitives of all of them
+        tot += (stage == kStFillC2P ? 1.0 : nst - 1) * (2 * nv * W * (grown - valid) + nv * W * valid + nq * W * grown);
+        break;
       case kStC2P: tot += (nv + nq) * W * grown; break;
       case kStC2POnly: tot += (scheme ? nst - 1 : 1.0) * (nv + nq) * W * grown; break;
       case kStCfl: tot += 5 * W * valid; break;

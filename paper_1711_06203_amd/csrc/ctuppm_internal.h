@@ -12,6 +12,7 @@ constexpr int kMaxSpec = 16;
 constexpr int kMaxV = kNV + kMaxSpec;
 constexpr int kNG = 4;     // ghost layers
 constexpr int kBlock = 256;  // threads per block = items per chunk
+constexpr int kTicks = 16;   // counters a launch's blocks count themselves off on, per problem
 constexpr int kSlots = 64;   // signal-speed max accumulators per problem (spread atomics)
 
 // Work regions of a box (n valid cells per direction), as (origin, extent):
@@ -75,6 +76,9 @@ struct ProbDev {
   // running max of the signal speed as bit patterns (>= 0), one 128-byte
   // line per slot so blocks of one launch do not contend on one address
   unsigned long long smax[kSlots][16];
+  // blocks of the conversion (0) and of the update (1) that have ended, one
+  // line per counter; zero between launches
+  unsigned tick[2][kTicks + 1][32];
 };
 
 // One box of a step set.
@@ -174,6 +178,7 @@ enum Stage : int {
   kStTraceX, kStTraceY, kStTraceZ, kStRiemX, kStRiemY, kStRiemZ, kStT1X, kStT1Y, kStT1Z,
   kStT2X, kStT2Y, kStT2Z, kStUpdate, kStFlip,
   kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kStRiem3, kStT2All, kStMolFlux,
+  kStFillC2P, kStFillC2POnly,
   kNumStages
 };
 
@@ -193,6 +198,7 @@ __host__ __device__ inline int stage_region(int stage) {
     case kStTraceX: case kStTraceY: case kStTraceZ: return kCells1;
     case kStReconX: case kStReconY: case kStReconZ: return kCells1;
     case kStMolUpdate: case kStMolFlux: return kValid;
+    case kStFillC2P: case kStFillC2POnly: return kValid;  // and the copy tags
     case kStRiemX: case kStRiemY: return kCells1;  // whole rows / planes of stores
     case kStT1X: return kFace0;
     case kStT1Y: return kFace1;
@@ -221,10 +227,15 @@ struct Launch {
   int lim = 0;         // reconstruction variant: 0 CW84, 1 Colella & Sekora, 2 CW84 + contact steepening
   int sp = 0;          // a problem of the launch carries passive species (merged tracing and stage 1)
   int mol = 0;         // method-of-lines scheme (the species stage stores edge values)
+  int fin = 0;         // the last block of the conversion takes dt, of the update commits
+  int guard = 0;       // that commit is guarded
   int spstage = 0;     // the species stage traces the species (the merged kernels leave them)
 };
 
 hipError_t launch_stage(int stage, const Launch& L);
+// Ghost fill and conversion in one launch: L over valid cells, T the copy tags
+// (tblocks blocks, a multiple of 8, after L.grid).
+hipError_t launch_fill_c2p(const Launch& L, const Segs& T, int tblocks, bool cfl);
 // Two-level kernels: gather (which: 0 = state at t^n into ct0, 1 = new state
 // into ct1), coarse-to-fine interpolation at theta, register init from the
 // coarse fluxes, register accumulation of the fine fluxes, average down,

@@ -80,6 +80,17 @@ CTU_DEV void for_each_unit(const Segs& L, F&& f) {
     unit_body((const March*)L.s[s].work, L.s[s].boxes, c - L.beg[s], f);
   });
 }
+// Likewise by blocks `block` of `blocks`: f(unit, its box, the unit's index in
+// its problem's part of the launch, the number of units there).
+template <class F>
+CTU_DEV void for_each_unit_of(const Segs& L, int block, int blocks, F&& f) {
+  for_each_chunk(L.beg[L.n], block, blocks, [&](int c) {
+    const int s = seg_of(L, c);
+    unit_body((const March*)L.s[s].work, L.s[s].boxes, c - L.beg[s], [&](const March& M, const BoxRec& B) {
+      f(M, B, c - L.beg[s], L.beg[s + 1] - L.beg[s]);
+    });
+  });
+}
 
 // Visit the march units of a launch once per direction: f(direction, unit, its
 // box).  A third of the grid (a multiple of 8 blocks) takes all units along
@@ -97,11 +108,15 @@ CTU_DEV void for_each_unit_dir(const Segs& L, F&& f) {
 
 // Visit the tag chunks of a launch: f(chunk, its segment).
 template <class F>
-CTU_DEV void for_each_tag_chunk(const Segs& L, F&& f) {
-  for_each_chunk(L.beg[L.n], [&](int c) {
+CTU_DEV void for_each_tag_chunk(const Segs& L, int block, int blocks, F&& f) {
+  for_each_chunk(L.beg[L.n], block, blocks, [&](int c) {
     const int s = seg_of(L, c);
     f(((const Chunk*)L.s[s].work)[c - L.beg[s]], L.s[s]);
   });
+}
+template <class F>
+CTU_DEV void for_each_tag_chunk(const Segs& L, F&& f) {
+  for_each_tag_chunk(L, blockIdx.x, gridDim.x, f);
 }
 
 // Visit the (i, j, k) items of a march unit in region `kind`; f(i, j, k) is
@@ -259,66 +274,6 @@ CTU_DEV void flush_max(ProbDev* P, double m, double* lds) {
   if (threadIdx.x == 0) atomicMax(&P->smax[blockIdx.x % kSlots][0], (unsigned long long)__double_as_longlong(bm));
 }
 
-// Primitive state (rho, u, v, w, p, c) with floors (WQ: stored for every
-// grown cell) and the signal speed max_d (|u_d| + c) / dx_d of the valid
-// cells (CFL: reduced per problem by wave shuffles, LDS and a 64-bit atomic
-// max on the bit pattern; non-negative doubles order like unsigned integers,
-// so the max is exact and order-free).  The batched forms do both in one pass;
-// the per-box form, whose boxes share one scratch, reduces first (CFL only)
-// and stores q box by box after dt is known.
-template <bool WQ, bool CFL>
-__global__ __launch_bounds__(kBlock) void k_c2p(const Segs L, int arr) {
-  __shared__ double lds[kBlock / 64];
-  double smax = 0.0;
-  ProbDev* curP = nullptr;
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
-    ProbDev* P = B.P;
-    if (P != curP) {  // block-uniform: flush the running max of the previous problem
-      if (CFL && curP) flush_max(curP, smax, lds);
-      smax = 0.0;
-      curP = P;
-    }
-    const Geo g(B.n, B.ns);
-    const gdbl* __restrict__ U = gp(state_arr(B, arr));
-    gdbl* __restrict__ q = g.q(B.scr);
-    CProb* Pc = cprob(P);
-    const bool summed = Pc->scheme != 0;
-    const double gamma = Pc->gamma, gm1 = Pc->gm1, sd = Pc->small_dens, sp = Pc->small_pres;
-    const double rdx = Pc->rdx[0], rdy = Pc->rdx[1], rdz = Pc->rdx[2];
-    unsigned long long hd = 0, hp = 0;
-    march(WQ ? kGrown : kValid, B, M, [&](int i, int j, int k) {
-      const int o = g.g(i, j, k);
-      double rho = U[o];
-      if (rho < sd) { rho = sd; ++hd; }
-      const double u = U[g.gcomp + o] / rho, v = U[2 * g.gcomp + o] / rho, w = U[3 * g.gcomp + o] / rho;
-      const double ke = 0.5 * rho * ((u * u + v * v) + w * w);
-      double p = gm1 * (U[4 * g.gcomp + o] - ke);
-      if (p < sp) { p = sp; ++hp; }
-      const double cs = sqrt(gamma * p / rho);
-      if (WQ) {
-        q[o] = rho;
-        q[g.gcomp + o] = u;
-        q[2 * g.gcomp + o] = v;
-        q[3 * g.gcomp + o] = w;
-        q[4 * g.gcomp + o] = p;
-        q[5 * g.gcomp + o] = cs;
-        for (int is = 0; is < g.ns; ++is) q[(6 + is) * g.gcomp + o] = U[(kNV + is) * g.gcomp + o] / rho;
-      }
-      if (CFL && i >= 0 && i < B.n[0] && j >= 0 && j < B.n[1] && k >= 0 && k < B.n[2]) {
-        const double sx = (fabs(u) + cs) * rdx;
-        const double sy = (fabs(v) + cs) * rdy;
-        const double sz = (fabs(w) + cs) * rdz;
-        smax = dmax(smax, summed ? (sx + sy) + sz : dmax(sx, dmax(sy, sz)));
-      }
-    });
-    if (WQ) {
-      count(&P->cnt[0], hd);
-      count(&P->cnt[1], hp);
-    }
-  });
-  if (CFL && curP) flush_max(curP, smax, lds);
-}
-
 // The step's dt and its per-direction factors (the same roundings as writing
 // them out where they are used).
 CTU_DEV void set_dt(ProbDev* P, double dt) {
@@ -331,18 +286,174 @@ CTU_DEV void set_dt(ProbDev* P, double dt) {
   }
 }
 
-__global__ void k_dt(const Segs L) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= L.n) return;
-  ProbDev* P = L.s[t].P;
-  unsigned long long bits = 0ull;
-  for (int q = 0; q < kSlots; ++q) {
-    bits = P->smax[q][0] > bits ? P->smax[q][0] : bits;
-    P->smax[q][0] = 0ull;
+// dt of a problem from its signal-speed slots, by one wave (lane q takes slot
+// q); the slots are cleared for the next step.
+CTU_DEV void dt_wave(ProbDev* P, int lane) {
+  static_assert(kSlots == 64, "one slot per lane");
+  unsigned long long* slot = &P->smax[lane][0];
+  unsigned long long bits = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  *slot = 0ull;
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned long long o = __shfl_xor(bits, off, 64);
+    bits = o > bits ? o : bits;
   }
   const double s = __longlong_as_double((long long)bits);
-  set_dt(P, P->fixed_dt > 0.0 ? P->fixed_dt : P->cfl / s);
+  if (lane == 0) set_dt(P, P->fixed_dt > 0.0 ? P->fixed_dt : P->cfl / s);
 }
+
+// Whether this block's unit is the last of its problem's `n` units of a launch
+// to end (true on the first wave only): the work of a one-block launch can
+// then follow in the same launch, which saves a small step the launch (5 us
+// each for dt and the commit, of a 32^3 box's 73).  Blocks count themselves off
+// on kTicks lines, then on one more, so no line takes more than a sixteenth
+// of them.  Every wave waits for its own atomics and stores first; the
+// counters and slots the finishing block reads are only ever updated by
+// device-scope atomics, so they need no cache write-back.
+CTU_DEV bool last_unit(ProbDev* P, int kind, int unit, int n) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x >= 64) return false;
+  int last = 0;
+  if (threadIdx.x == 0) {
+    auto count_off = [](unsigned* c, unsigned of) {
+      if (__hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != of - 1) return false;
+      __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next step
+      return true;
+    };
+    const int line = unit % kTicks;
+    last = count_off(&P->tick[kind][line][0], (n - line + kTicks - 1) / kTicks) &&
+           count_off(&P->tick[kind][kTicks][0], n < kTicks ? n : kTicks);
+  }
+  return __builtin_amdgcn_readfirstlane(last) != 0;
+}
+
+// Primitive state (rho, u, v, w, p, c) of a conserved one with floors
+// (counted in hd, hp), stored to q (WQ); returns the signal speed
+// max_d (|u_d| + c) / dx_d (or the sum over d) if CFL.  X_s = rho X_s / rho of
+// species s, conserved value US(s).
+template <bool WQ, bool CFL, class F>
+CTU_DEV double prim_cell(CProb* P, const Geo& g, gdbl* __restrict__ q, int o, double rho, double mu, double mv,
+                         double mw, double E, F&& US, unsigned long long& hd, unsigned long long& hp) {
+  if (rho < P->small_dens) { rho = P->small_dens; ++hd; }
+  const double u = mu / rho, v = mv / rho, w = mw / rho;
+  const double ke = 0.5 * rho * ((u * u + v * v) + w * w);
+  double p = P->gm1 * (E - ke);
+  if (p < P->small_pres) { p = P->small_pres; ++hp; }
+  const double cs = sqrt(P->gamma * p / rho);
+  if (WQ) {
+    q[o] = rho;
+    q[g.gcomp + o] = u;
+    q[2 * g.gcomp + o] = v;
+    q[3 * g.gcomp + o] = w;
+    q[4 * g.gcomp + o] = p;
+    q[5 * g.gcomp + o] = cs;
+    for (int is = 0; is < g.ns; ++is) q[(6 + is) * g.gcomp + o] = US(is) / rho;
+  }
+  if (!CFL) return 0.0;
+  const double sx = (fabs(u) + cs) * P->rdx[0];
+  const double sy = (fabs(v) + cs) * P->rdx[1];
+  const double sz = (fabs(w) + cs) * P->rdx[2];
+  return P->scheme != 0 ? (sx + sy) + sz : dmax(sx, dmax(sy, sz));
+}
+
+// Primitives of the cells of a region (WQ: stored), and the signal speed of
+// the valid cells (CFL: reduced per problem by wave shuffles, LDS and a 64-bit
+// atomic max on the bit pattern; non-negative doubles order like unsigned
+// integers, so the max is exact and order-free).  FIN: the last block also
+// takes dt.
+template <bool WQ, bool CFL, bool FIN, int REGION>
+CTU_DEV void c2p_units(const Segs& L, int arr, int block, int blocks, double* lds) {
+  double smax = 0.0;
+  ProbDev* curP = nullptr;
+  for_each_unit_of(L, block, blocks, [&](const March& M, const BoxRec& B, int unit, int units) {
+    ProbDev* P = B.P;
+    if (P != curP) {  // block-uniform: flush the running max of the previous problem
+      if (CFL && curP) flush_max(curP, smax, lds);
+      smax = 0.0;
+      curP = P;
+    }
+    const Geo g(B.n, B.ns);
+    const gdbl* __restrict__ U = gp(state_arr(B, arr));
+    gdbl* __restrict__ q = g.q(B.scr);
+    unsigned long long hd = 0, hp = 0;
+    march(REGION, B, M, [&](int i, int j, int k) {
+      const int o = g.g(i, j, k);
+      const double sig = prim_cell<WQ, CFL>(
+          cprob(P), g, q, o, U[o], U[g.gcomp + o], U[2 * g.gcomp + o], U[3 * g.gcomp + o], U[4 * g.gcomp + o],
+          [&](int is) { return U[(kNV + is) * g.gcomp + o]; }, hd, hp);
+      if (CFL && (REGION == kValid || (i >= 0 && i < B.n[0] && j >= 0 && j < B.n[1] && k >= 0 && k < B.n[2])))
+        smax = dmax(smax, sig);
+    });
+    if (WQ) {
+      count(&P->cnt[0], hd);
+      count(&P->cnt[1], hp);
+    }
+    if (CFL && FIN) {
+      flush_max(P, smax, lds);
+      smax = 0.0;
+      if (last_unit(P, 0, unit, units)) dt_wave(P, threadIdx.x);
+    }
+  });
+  if (CFL && !FIN && curP) flush_max(curP, smax, lds);
+}
+
+// The batched forms convert and reduce in one pass; the per-box form, whose
+// boxes share one scratch, reduces first (CFL only) and stores q box by box
+// after dt is known.
+template <bool WQ, bool CFL, bool FIN>
+__global__ __launch_bounds__(kBlock) void k_c2p(const Segs L, int arr) {
+  __shared__ double lds[kBlock / 64];
+  c2p_units<WQ, CFL, FIN, WQ ? kGrown : kValid>(L, arr, blockIdx.x, gridDim.x, lds);
+}
+
+// Ghost fill and conversion in one launch, for small sets all of whose ghost
+// cells are copies of valid cells (periodic domains): the first blocks convert
+// the valid cells, the others take the copy tags T, storing each source cell's
+// state to the ghost cell and its primitives to q, so neither waits for the
+// other.  One 48^3 box 20.5 -> 11.7 us; at 256^3 it would take 0.84 ms against
+// 0.60 for the two launches, whose conversion writes whole rows of q.
+template <bool CFL>
+__global__ __launch_bounds__(kBlock) void k_fill_c2p(const Segs L, const Segs T, int vblocks, int arr) {
+  __shared__ double lds[kBlock / 64];
+  if (int(blockIdx.x) < vblocks) {
+    c2p_units<true, CFL, CFL, kValid>(L, arr, blockIdx.x, vblocks, lds);
+    return;
+  }
+  for_each_tag_chunk(T, blockIdx.x - vblocks, gridDim.x - vblocks, [&](const Chunk& ch, const Seg& S) {
+    const FillTag G = ((const FillTag*)S.tags)[ch.box];
+    const int t = ch.start + threadIdx.x;
+    if (t >= G.ext[0] * G.ext[1] * G.ext[2]) return;
+    const int i = G.lo[0] + t % G.ext[0];
+    const int r = t / G.ext[0];
+    const int j = G.lo[1] + r % G.ext[1];
+    const int k = G.lo[2] + r / G.ext[1];
+    const BoxRec& D = S.boxes[G.dst];
+    const BoxRec& Sb = S.boxes[G.src];
+    const Geo gd(D.n, D.ns), gs(Sb.n, Sb.ns);
+    const gdbl* __restrict__ src = gp(state_arr(Sb, arr)) + gs.g(i + G.off[0], j + G.off[1], k + G.off[2]);
+    const int di = gd.g(i, j, k);
+    gdbl* __restrict__ dst = gp(state_arr(D, arr)) + di;
+    double v[5];
+#pragma unroll
+    for (int m = 0; m < kNV; ++m) v[m] = src[m * gs.gcomp];
+#pragma unroll
+    for (int m = 0; m < kNV; ++m) dst[m * gd.gcomp] = v[m];
+    unsigned long long hd = 0, hp = 0;
+    prim_cell<true, false>(
+        cprob(D.P), gd, gd.q(D.scr), di, v[0], v[1], v[2], v[3], v[4],
+        [&](int is) {
+          const double x = src[(kNV + is) * gs.gcomp];
+          dst[(kNV + is) * gd.gcomp] = x;
+          return x;
+        },
+        hd, hp);
+    count(&D.P->cnt[0], hd);
+    count(&D.P->cnt[1], hp);
+  });
+}
+
+// One wave per problem.
+__global__ __launch_bounds__(64) void k_dt(const Segs L) { dt_wave(L.s[blockIdx.x].P, threadIdx.x); }
 
 // A caller's dt (a device double) for the next advance of a problem: the
 // coarse level takes it, a fine level half of it.
@@ -357,11 +468,8 @@ __global__ void k_set_dt(ProbDev* Pc, ProbDev* Pf, const double* dt) {
 // failure count grew is not committed: the old state stays current (it is
 // intact in the other fab), the rejection is counted and mirrored to the
 // host-mapped flag the host reads without synchronising.
-__global__ void k_flip(const Segs L, int guard) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= L.n) return;
-  ProbDev* P = L.s[t].P;
-  const unsigned long long nf = P->cnt[4];
+CTU_DEV void flip(ProbDev* P, int guard) {
+  const unsigned long long nf = __hip_atomic_load(&P->cnt[4], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (guard && nf != P->fail_mark) {
     P->rejected += 1;
     if (P->fail_step == P->nsteps) P->fail_step = -1;  // the test hook fires once
@@ -371,6 +479,16 @@ __global__ void k_flip(const Segs L, int guard) {
     P->nsteps += 1;
   }
   P->fail_mark = nf;
+}
+
+__global__ void k_flip(const Segs L, int guard) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < L.n) flip(L.s[t].P, guard);
+}
+
+// Commit at the end of the update's last block.
+CTU_DEV void finish_update(ProbDev* P, int guard, int unit, int n) {
+  if (last_unit(P, 1, unit, n) && threadIdx.x == 0) flip(P, guard);
 }
 
 // ---------------------------------------------------------------- flattening
@@ -1118,8 +1236,9 @@ __global__ __launch_bounds__(kBlock) void k_trans2_3(const Segs L) {
 // Conservative update U^{n+1} = U^n + sum_d dt/dx_d (F_lo - F_hi) in the order
 // x, y, z, the trapezoid gravity corrector on rho w then rho E, and the
 // failure check (rho < small_dens, p < small_pres or a non-finite value).
-__global__ __launch_bounds__(kBlock) void k_update(const Segs L) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
+template <bool FIN>
+__global__ __launch_bounds__(kBlock) void k_update(const Segs L, int guard) {
+  for_each_unit_of(L, blockIdx.x, gridDim.x, [&](const March& M, const BoxRec& B, int unit, int units) {
     CProb* P = cprob(B.P);
     const Geo g(B.n, B.ns);
     const gdbl* __restrict__ U = gp(B.U[P->cur]);
@@ -1171,6 +1290,7 @@ __global__ __launch_bounds__(kBlock) void k_update(const Segs L) {
       nbad += bad ? 1ull : 0ull;
     });
     count(&B.P->cnt[4], nbad);
+    if (FIN) finish_update(B.P, guard, unit, units);
   });
 }
 
@@ -1328,9 +1448,10 @@ CTU_DEV bool mol_cell(CProb* P, const Geo& g, const gdbl* __restrict__ Us, const
 // rho w) of Us; written as T, or as U0 + c (T - U0) with U0 the current fab
 // (the convex combinations of the SSP methods, in a form that keeps a
 // constant state exactly constant).  Failures are counted as in k_update.
+template <bool FIN>
 __global__ __launch_bounds__(kBlock) void k_mol_update(const Segs L, int arr,
-                                                       int out, int comb, double c, int last) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
+                                                       int out, int comb, double c, int last, int guard) {
+  for_each_unit_of(L, blockIdx.x, gridDim.x, [&](const March& M, const BoxRec& B, int unit, int units) {
     CProb* P = cprob(B.P);
     const Geo g(B.n, B.ns);
     const gdbl* __restrict__ Us = gp(state_arr(B, arr));
@@ -1371,6 +1492,7 @@ __global__ __launch_bounds__(kBlock) void k_mol_update(const Segs L, int arr,
       nbad += bad ? 1ull : 0ull;
     });
     count(&B.P->cnt[4], nbad);
+    if (FIN) finish_update(B.P, guard, unit, units);
   });
 }
 
@@ -1412,10 +1534,10 @@ CTU_DEV void face_pair(const BoxRec& B, const Geo& g, CProb* P, int o, int x, do
   }
 }
 
-template <int RS>
+template <int RS, bool FIN>
 __global__ __launch_bounds__(kBlock) void k_mol_flux_update(const Segs L, int arr, int out, int comb, double c,
-                                                            int last) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) {
+                                                            int last, int guard) {
+  for_each_unit_of(L, blockIdx.x, gridDim.x, [&](const March& M, const BoxRec& B, int unit, int units) {
     CProb* P = cprob(B.P);
     const Geo g(B.n, B.ns);
     const gdbl* __restrict__ Us = gp(state_arr(B, arr));
@@ -1436,6 +1558,7 @@ __global__ __launch_bounds__(kBlock) void k_mol_flux_update(const Segs L, int ar
       nbad += bad ? 1ull : 0ull;
     });
     count(&B.P->cnt[4], nbad);
+    if (FIN) finish_update(B.P, guard, unit, units);
   });
 }
 
@@ -1692,7 +1815,7 @@ const char* stage_name(int s) {
       "trace_x", "trace_y", "trace_z", "riemann_x", "riemann_y", "riemann_z",
       "trans1_x", "trans1_y", "trans1_z", "trans2_x", "trans2_y", "trans2_z", "update", "flip",
       "recon_x", "recon_y", "recon_z", "mol_update", "trace_xyz", "trans1_xyz", "recon_xyz", "species_xyz",
-      "riemann_xyz", "trans2_xyz", "mol_flux_update"};
+      "riemann_xyz", "trans2_xyz", "mol_flux_update", "fill_cons2prim_cfl", "fill_cons2prim"};
   return (s >= 0 && s < kNumStages) ? names[s] : "?";
 }
 
@@ -1710,17 +1833,30 @@ hipError_t launch_stage(int stage, const Launch& L) {
     case kStBcX: k_bc<0><<<grid, block, 0, s>>>(G, L.arr); break;
     case kStBcY: k_bc<1><<<grid, block, 0, s>>>(G, L.arr); break;
     case kStBcZ: k_bc<2><<<grid, block, 0, s>>>(G, L.arr); break;
-    case kStC2P: k_c2p<true, true><<<grid, block, 0, s>>>(G, L.arr); break;
-    case kStCfl: k_c2p<false, true><<<grid, block, 0, s>>>(G, L.arr); break;
-    case kStC2POnly: k_c2p<true, false><<<grid, block, 0, s>>>(G, L.arr); break;
+    case kStC2P:
+      if (L.fin) k_c2p<true, true, true><<<grid, block, 0, s>>>(G, L.arr);
+      else k_c2p<true, true, false><<<grid, block, 0, s>>>(G, L.arr);
+      break;
+    case kStCfl: k_c2p<false, true, false><<<grid, block, 0, s>>>(G, L.arr); break;
+    case kStC2POnly: k_c2p<true, false, false><<<grid, block, 0, s>>>(G, L.arr); break;
     case kStReconX: CTU_LIM(k_recon, 0); break;
     case kStReconY: CTU_LIM(k_recon, 1); break;
     case kStReconZ: CTU_LIM(k_recon, 2); break;
+#define CTU_ARGS (G, L.arr, L.out, L.comb, L.c, L.last, L.guard)
     case kStMolFlux:
-      if (L.rs) k_mol_flux_update<1><<<grid, block, 0, s>>>(G, L.arr, L.out, L.comb, L.c, L.last);
-      else k_mol_flux_update<0><<<grid, block, 0, s>>>(G, L.arr, L.out, L.comb, L.c, L.last);
+      if (L.fin) {
+        if (L.rs) k_mol_flux_update<1, true><<<grid, block, 0, s>>> CTU_ARGS;
+        else k_mol_flux_update<0, true><<<grid, block, 0, s>>> CTU_ARGS;
+      } else {
+        if (L.rs) k_mol_flux_update<1, false><<<grid, block, 0, s>>> CTU_ARGS;
+        else k_mol_flux_update<0, false><<<grid, block, 0, s>>> CTU_ARGS;
+      }
       break;
-    case kStMolUpdate: k_mol_update<<<grid, block, 0, s>>>(G, L.arr, L.out, L.comb, L.c, L.last); break;
+    case kStMolUpdate:
+      if (L.fin) k_mol_update<true><<<grid, block, 0, s>>> CTU_ARGS;
+      else k_mol_update<false><<<grid, block, 0, s>>> CTU_ARGS;
+      break;
+#undef CTU_ARGS
 #define CTU_LIM3(K)                                                         \
   (L.lim == 1   ? K<1><<<grid, block, 0, s>>>(G)                            \
    : L.lim == 2 ? K<2><<<grid, block, 0, s>>>(G)                            \
@@ -1780,10 +1916,21 @@ hipError_t launch_stage(int stage, const Launch& L) {
     case kStT2All: CTU_RS3(k_trans2_3); break;
 #undef CTU_RS3
 #undef CTU_RS
-    case kStUpdate: k_update<<<grid, block, 0, s>>>(G); break;
+    case kStUpdate: 
+      if (L.fin) k_update<true><<<grid, block, 0, s>>>(G, L.guard);
+      else k_update<false><<<grid, block, 0, s>>>(G, 0);
+      break;
     default: return hipErrorInvalidValue;
   }
 #undef CTU_LIM
+  return hipGetLastError();
+}
+
+// (with the CFL reduction its last block takes dt: the sets that use it do)
+hipError_t launch_fill_c2p(const Launch& L, const Segs& T, int tblocks, bool cfl) {
+  const dim3 grid(L.grid + tblocks), block(kBlock);
+  if (cfl) k_fill_c2p<true><<<grid, block, 0, L.stream>>>(L.segs, T, L.grid, L.arr);
+  else k_fill_c2p<false><<<grid, block, 0, L.stream>>>(L.segs, T, L.grid, L.arr);
   return hipGetLastError();
 }
 
@@ -1851,7 +1998,7 @@ hipError_t launch_set_dt(ProbDev* Pc, ProbDev* Pf, const double* dt, hipStream_t
 
 hipError_t launch_dt(const Segs& L, hipStream_t s) {
   if (L.n <= 0) return hipSuccess;
-  k_dt<<<1, 64, 0, s>>>(L);
+  k_dt<<<L.n, 64, 0, s>>>(L);
   return hipGetLastError();
 }
 

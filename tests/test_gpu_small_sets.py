@@ -1,0 +1,86 @@
+"""Small sets take dt and the commit in the last blocks of the conversion and
+the update, and periodic ones their ghost fill in the conversion's launch.
+Each value takes the same operations as in the launches of their own that
+larger sets use, so states, ghost cells, dt and counters are compared bit for
+bit, with the oracle and with the split stages."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1711_06203_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_1711_06203_amd import ctuppm
+    c = ctuppm.Context()
+    yield c
+    c.set_fused(1)
+    c.close()
+
+
+def _step(ctx, prob, form, fused, steps):
+    from paper_1711_06203_amd import ctuppm
+    ctx.set_fused(fused)
+    s = ctuppm.Solver(ctx, prob, form=form)
+    s.step(steps)
+    out = [s.state(), s.counters(), np.array([s.dt()]), s.UA.cpu().numpy()]  # with the ghost cells of U^n
+    s.close()
+    return out
+
+
+@pytest.mark.parametrize("form", ["per_box", "batched", "graph"])
+@pytest.mark.parametrize("scheme", [0, 1, 2])
+@pytest.mark.parametrize("n,box", [
+    ((4, 4, 4), (4, 4, 4)),          # the smallest periodic extent: every ghost cell its own box's
+    ((15, 4, 5), (15, 4, 5)),        # fewer update units than counters
+    ((16, 16, 16), (16, 16, 16)),    # sixteen units, one a counter
+    ((17, 15, 16), (17, 15, 16)),
+    ((20, 9, 14), (7, 9, 5)),        # ghost cells from several boxes
+])
+def test_dt_commit_and_ghosts(ctx, form, scheme, n, box):
+    prob = W.kelvin_helmholtz(n=n, box=box, seed=7, nspec=scheme)
+    prob.scheme = scheme
+    got = _step(ctx, prob, form, 1, 3)
+    split = _step(ctx, prob, form, 0, 3)
+    ref, dts, _ = oracle.run_problem(prob, 3)
+    assert np.array_equal(got[0], ref) and got[2][0] == dts[-1]
+    for a, b in zip(got, split):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("form", ["per_box", "batched", "graph"])
+@pytest.mark.parametrize("scheme", [0, 1])
+def test_rejected_step_is_not_committed(ctx, form, scheme):
+    from paper_1711_06203_amd import ctuppm
+    ctx.set_fused(1)
+    prob = W.serving_request(seed=4, n=11)
+    prob.scheme = scheme
+    s = ctuppm.Solver(ctx, prob, form=form)
+    s.set_fail_hook(1)
+    s.step_guarded(1)
+    with pytest.raises(ctuppm.Rejected):
+        for _ in range(50):
+            s.step_guarded(1)
+            ctx.torch.cuda.synchronize()
+    assert s.rejections() == 1
+    s.step_guarded(1)  # the hook fired once: the step is redone
+    assert s.counters()[5] == 2
+    ref, _, _ = oracle.run_problem(prob, 2)
+    assert np.array_equal(s.state(), ref)
+    s.close()
+
+
+def test_many_small_problems_in_one_set(ctx):
+    from paper_1711_06203_amd import ctuppm
+    ctx.set_fused(1)
+    probs = [W.serving_request(seed=s, n=4 + s % 9) for s in range(21)]  # two launches of segments
+    solvers = [ctuppm.Solver(ctx, p, form="batched") for p in probs]
+    for _ in range(3):
+        ctx.step(solvers, "batched", 1, guarded=True)
+    for s, p in zip(solvers, probs):
+        ref, dts, _ = oracle.run_problem(p, 3)
+        assert np.array_equal(s.state(), ref) and s.dt() == dts[-1]
+        s.close()
