@@ -431,7 +431,6 @@ struct Packer {
     if (!v.empty()) std::memcpy(buf.data() + off, v.data(), v.size() * sizeof(T));
     return v.empty() ? nullptr : (T*)(dbase + off);
   }
-  void reserve_bytes(size_t n) { buf.resize(align256(buf.size()) + n); }
 };
 
 // Bytes the packer reserves for an array of n T's.
@@ -1096,16 +1095,13 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
         const int planes = z == 0 || c->region_set[k] ? c->region_planes[k] : (k == kGrown ? 2 : 1);
         std::vector<March> u;
         T.upre[z][k].assign(nb + 1, 0);
-        long long cap = 0;
         for (int b = 0; b < nb; ++b) {
           int org[3], ext[3];
           region_of(k, recs[0][b].n, org, ext);
           march_region(u, b, org, ext, planes * zs[z], c->ytile);
           T.upre[z][k][b + 1] = int(u.size());
-          cap += max_units(recs[0][b].n, k);
         }
         T.units[z][k] = K.put(u);
-        K.reserve_bytes(packed<March>(cap) - packed<March>((long long)u.size()));
       }
     std::vector<FillTag> ft;
     std::vector<Chunk> fch;
