@@ -417,7 +417,10 @@ int ctuppm_set_wave_boxes(ctuppm_ctx* ctx, int boxes);
  * the first transverse stage of the three directions (CTU) in one kernel
  * that reads each normal flux array once, and the normal and the final fluxes
  * of the three directions in one launch each (the method of lines without
- * species takes its normal fluxes inside the update instead); 2, as 1 with the species traced
+ * species takes its normal fluxes inside the update instead; small sets take
+ * the face states and the first transverse stage in launches with blocks of
+ * one direction each, species included: stages "trace_dir", "recon_dir",
+ * "trans1_dir"); 2, as 1 with the species traced
  * inside the merged kernels (no species stage); off (0), a flattening kernel
  * and one kernel per direction.  Results are the same bits in every mode
  * (each face takes the same arithmetic); captured graphs are dropped.

@@ -95,6 +95,9 @@ def tune(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver], candidates: Iter
 MERGED: Dict[str, Tuple[str, ...]] = {
     "riemann_xyz": ("riemann_x", "riemann_y", "riemann_z"),
     "trans2_xyz": ("trans2_x", "trans2_y", "trans2_z"),
+    "trace_dir": ("trace_xyz",),
+    "trans1_dir": ("trans1_xyz",),
+    "recon_dir": ("recon_xyz",),
     "mol_flux_update": ("riemann_x", "riemann_y", "riemann_z", "mol_update"),
 }
 STAGE_CANDIDATES: Tuple[int, ...] = (1, 2, 4, 8)

@@ -132,6 +132,7 @@ struct StepSet {
   int species = 0;  // 1 when a problem of the set carries passive species
   int nboxes = 0;
   int copies = 0;   // ghost fill and conversion in one launch: fin, and every ghost cell is a copy of a valid cell
+  int dirs = 0;     // tracing and stage 1 by blocks of one direction each
   int fin = 0;      // dt and the commit by the last blocks of the conversion and the update
   int zvar = 0;     // work-unit variant of its launches (LevelTables)
   hipGraph_t graph[2] = {nullptr, nullptr};  // captured step, unguarded / guarded
@@ -353,6 +354,12 @@ void march_region(std::vector<March>& out, int box, const int org[3], const int 
 // mix of ten problems, 19000 units: 154 -> 165 us).
 constexpr int kFinUnits = 2048;
 
+// Sets of at most this many stage-1 units leave CUs idle and take tracing and
+// stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
+// us, 32^3 55 -> 50, 48^3 (500 units) 85.6 -> 84.5, 56^3 (812) 127 -> 120; 27
+// boxes of 16^3 (972) 121 -> 123, 72^3 (1628) 220 -> 221.
+constexpr int kDirUnits = 832;
+
 constexpr int kMinUnitsPerCu = 8;  // deeper work units only while a level keeps this many per CU
 
 // Most march units one box region can have under any tuning (one row per
@@ -465,8 +472,10 @@ int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool per
   Launch L{};
   L.segs = G;
   L.grid = grid_for(c, G.beg[G.n], persistent);
-  // the merged normal and final fluxes visit their units once per direction
-  if (stage == kStRiem3 || stage == kStT2All) L.grid *= 3;
+  // these visit their units once per direction
+  if (stage == kStRiem3 || stage == kStT2All || stage == kStTraceDir || stage == kStT1Dir ||
+      stage == kStReconDir)
+    L.grid *= 3;
   L.stream = s;
   L.arr = A.arr;
   L.out = A.out;
@@ -1222,10 +1231,11 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   long long deep = 0;
   for (Problem* P : S->probs) deep += P->lt[level].upre[0][kCells1T].back();
   S->zvar = S->form == CTUPPM_FORM_PER_BOX ? 1 : (deep < (long long)kMinUnitsPerCu * c->num_cus ? 2 : 0);
-  long long upd = 0, ghosts = 0;
+  long long upd = 0, ghosts = 0, cells1 = 0;
   for (Problem* P : S->probs) {
     const LevelTables& T = P->lt[level];
     upd += T.upre[S->zvar][kValid].back();
+    cells1 += T.upre[S->zvar][kCells1].back();
     ghosts -= T.fcells;
     for (const auto& b : P->lev[level].boxes) {
       const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
@@ -1234,6 +1244,7 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   }
   S->fin = upd <= kFinUnits && (S->form != CTUPPM_FORM_PER_BOX || S->nboxes == 1) && S->form != CTUPPM_FORM_WAVES &&
            S->probs[0]->nlevels == 1;
+  S->dirs = S->fin && cells1 <= kDirUnits;
   S->copies = S->fin && ghosts == 0;
   *out = S.get();
   c->sets[key] = std::move(S);
@@ -1249,7 +1260,8 @@ const int kCellStagesSplit[] = {kStFlatten, kStTraceX, kStTraceY, kStTraceZ, kSt
                                 kStT1X, kStT1Y, kStT1Z, kStT2X, kStT2Y, kStT2Z, kStUpdate};
 const int kCellStagesFused[] = {kStTrace3, kStSpec3, kStRiem3, kStT1All, kStT2All, kStUpdate};
 
-std::vector<int> cell_stages(const ctuppm_ctx* c) {
+std::vector<int> cell_stages(const ctuppm_ctx* c, const StepSet* S) {
+  if (c->fused == 1 && S->dirs) return {kStTraceDir, kStRiem3, kStT1Dir, kStT2All, kStUpdate};
   if (c->fused) return std::vector<int>(std::begin(kCellStagesFused), std::end(kCellStagesFused));
   return std::vector<int>(std::begin(kCellStagesSplit), std::end(kCellStagesSplit));
 }
@@ -1318,7 +1330,9 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
   const bool fluxup = c->fused && !S->species;
   static const std::vector<int> fused_up = {kStRecon3}, fused = {kStRecon3, kStSpec3, kStRiem3};
   static const std::vector<int> split = {kStFlatten, kStReconX, kStReconY, kStReconZ, kStRiemX, kStRiemY, kStRiemZ};
-  const std::vector<int>& cells = fluxup ? fused_up : c->fused ? fused : split;
+  static const std::vector<int> dirs_up = {kStReconDir}, dirs = {kStReconDir, kStRiem3};
+  const bool by_dir = c->fused == 1 && S->dirs;
+  const std::vector<int>& cells = by_dir ? (fluxup ? dirs_up : dirs) : fluxup ? fused_up : c->fused ? fused : split;
   int rc;
   for (int r = 0; r < nst; ++r) {
     const int arr = r == 0 ? kArrCur : (r == 1 ? kArrW0 : kArrW1);
@@ -1429,7 +1443,7 @@ int enqueue_step(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard
   if (!S->fin && (rc = run_probs(c, S, s, false, 0))) return rc;
   for (const auto& g : box_groups(c, S)) {
     if (!own && (rc = run_range(c, S, s, kStC2POnly, g.first, g.second, timed))) return rc;
-    for (int st : cell_stages(c))
+    for (int st : cell_stages(c, S))
       if ((rc = run_range(c, S, s, st, g.first, g.second, timed, st == kStUpdate ? A : StageArgs()))) return rc;
   }
   return S->fin ? CTUPPM_OK : run_probs(c, S, s, true, guard);
@@ -1498,7 +1512,7 @@ int enqueue_two_level(ctuppm_ctx* c, Problem* P, TwoLevel* T, hipStream_t s, boo
   if ((rc = run_all(c, F, s, kStCfl, timed))) return rc;
   TLCHK(launch_dt2(P->dP, P->dPf, s));
   TLCHK(launch_gather(A, W.gtags, W.gch, W.ngch, 0, s));
-  for (int st : cell_stages(c))
+  for (int st : cell_stages(c, C))
     if ((rc = run_all(c, C, s, st, timed))) return rc;
   TLCHK(launch_reg_coarse(A, W.faces, W.nfaces, s));
   TLCHK(launch_gather(A, W.gtags, W.gch, W.ngch, 1, s));
@@ -1506,7 +1520,7 @@ int enqueue_two_level(ctuppm_ctx* c, Problem* P, TwoLevel* T, hipStream_t s, boo
     if ((rc = fill_arr(c, F, s, timed, kArrCur))) return rc;
     if ((rc = cf_fill(c, P, s, sub == 0 ? 0.0 : 0.5))) return rc;
     if ((rc = run_all(c, F, s, kStC2POnly, timed))) return rc;
-    for (int st : cell_stages(c))
+    for (int st : cell_stages(c, F))
       if ((rc = run_all(c, F, s, st, timed))) return rc;
     TLCHK(launch_reg_fine(A, W.faces, W.nfaces, s));
     if ((rc = run_probs(c, F, s, true, 0))) return rc;
@@ -1589,7 +1603,7 @@ int cfl_pass(ctuppm_ctx* c, StepSet* S, hipStream_t s) {
 int advance_cells(ctuppm_ctx* c, StepSet* S, hipStream_t s) {
   for (const auto& g : box_groups(c, S)) {
     int rc = run_range(c, S, s, kStC2POnly, g.first, g.second, c->timing);
-    for (int st : cell_stages(c)) {
+    for (int st : cell_stages(c, S)) {
       if (rc) break;
       rc = run_range(c, S, s, st, g.first, g.second, c->timing);
     }
@@ -2664,6 +2678,17 @@ int ctuppm_stage_bytes(ctuppm_ctx* c, int pid, int stage, double* bytes) {
         tot += nq * W * cells1 / (nn[d] + 2) * (nn[d] + 6) + W * cells1 + 2 * nv * W * face(d);
         break;
       }
+      case kStTraceDir: case kStReconDir:
+        // each direction's stencils, which hold those of its flattening term;
+        // phi stored once
+        for (int d = 0; d < 3; ++d)
+          tot += (stage == kStReconDir ? nst : 1.0) * (nq * W * cells1 / (nn[d] + 2) * (nn[d] + 6) + 2 * nv * W * face(d));
+        tot += (stage == kStReconDir ? nst : 1.0) * W * cells1;
+        break;
+      case kStT1Dir:
+        for (int a = 0; a < 3; ++a)
+          tot += 4 * nv * W * face(a) + nv * W * (half(a, (a + 1) % 3) + half(a, (a + 2) % 3));
+        break;
       case kStRiem3: tot += nst * 3 * nv * W * (face(0) + face(1) + face(2)); break;
       case kStT2All:
         for (int a = 0; a < 3; ++a) {

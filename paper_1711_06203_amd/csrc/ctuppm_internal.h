@@ -178,7 +178,7 @@ enum Stage : int {
   kStTraceX, kStTraceY, kStTraceZ, kStRiemX, kStRiemY, kStRiemZ, kStT1X, kStT1Y, kStT1Z,
   kStT2X, kStT2Y, kStT2Z, kStUpdate, kStFlip,
   kStReconX, kStReconY, kStReconZ, kStMolUpdate, kStTrace3, kStT1All, kStRecon3, kStSpec3, kStRiem3, kStT2All, kStMolFlux,
-  kStFillC2P, kStFillC2POnly,
+  kStFillC2P, kStFillC2POnly, kStTraceDir, kStT1Dir, kStReconDir,
   kNumStages
 };
 
@@ -208,7 +208,7 @@ __host__ __device__ inline int stage_region(int stage) {
     case kStT2Y: return kFin1;
     case kStT2Z: return kFin2;
     case kStUpdate: return kValid;
-    case kStRiem3: return kCells1;  // once per direction
+    case kStRiem3: case kStTraceDir: case kStT1Dir: case kStReconDir: return kCells1;  // once per direction
     case kStT2All: return kFin;     // once per direction
     default: return -1;
   }

@@ -746,6 +746,34 @@ __global__ __launch_bounds__(kBlock) void k_trace(const Segs L) {
   });
 }
 
+// Flattening and tracing for small sets: a third of the grid per direction,
+// each computing the flattening coefficient itself (the x blocks store it).
+// Three times the blocks of the merged tracing, each with under half its
+// chain of loads and arithmetic, which is all that a launch that leaves the
+// GPU mostly idle waits for.
+template <int LIM>
+__global__ __launch_bounds__(kBlock) void k_trace_dir(const Segs L) {
+  for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
+    const Geo g(B.n, B.ns);
+    CProb* P = cprob(B.P);
+    const gdbl* __restrict__ q = g.q(B.scr);
+    gdbl* __restrict__ phiout = g.phi(B.scr);
+    unsigned long long floors = 0;
+    march(kCells1, B, M, [&](int i, int j, int k) {
+      const double phi = flatten_cell(g, q, g.g(i, j, k));
+      if (d == 0) {
+        phiout[g.h(i, j, k)] = phi;
+        trace_cell<0, LIM>(B, g, P, i, j, k, phi, floors);
+      } else if (d == 1) {
+        trace_cell<1, LIM>(B, g, P, i, j, k, phi, floors);
+      } else {
+        trace_cell<2, LIM>(B, g, P, i, j, k, phi, floors);
+      }
+    });
+    count(&B.P->cnt[2], floors);
+  });
+}
+
 // One thread per cell of -1..n: the flattening coefficient (also stored, for
 // stage dumps), then tracing along x, then y, then z, so the cell's
 // primitives are read once for the flattening and the three directions (the
@@ -1109,6 +1137,26 @@ __global__ __launch_bounds__(kBlock) void k_trans1(const Segs L) {
   });
 }
 
+// Stage 1 for small sets: a third of the grid per direction, as k_trace_dir.
+template <int RS>
+__global__ __launch_bounds__(kBlock) void k_trans1_dir(const Segs L) {
+  for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
+    const Geo g(B.n, B.ns);
+    CProb* P = cprob(B.P);
+    unsigned long long fb = 0;
+    march(kCells1, B, M, [&](int i, int j, int k) {
+      if (d == 0) {
+        if (i >= 0) trans1_face<0, RS, true>(B, g, P, i, j, k, fb);
+      } else if (d == 1) {
+        if (j >= 0) trans1_face<1, RS, true>(B, g, P, i, j, k, fb);
+      } else {
+        if (k >= 0) trans1_face<2, RS, true>(B, g, P, i, j, k, fb);
+      }
+    });
+    count(&B.P->cnt[3], fb);
+  });
+}
+
 // Stage 1 along x, then y, then z, one thread per cell of -1..n (the lower
 // A-face of the cell, where the cell is not at -1 along A): each normal flux
 // array is read once instead of by two of the per-direction kernels.  SP as
@@ -1346,23 +1394,51 @@ CTU_DEV void recon_species(const BoxRec& B, const Geo& g, int o, int oh, double 
 // the arithmetic and every store after it, unconditionally and streaming (the
 // upper state of cell n and the lower state of cell -1 are never read).
 template <int D, int LIM>
+CTU_DEV void recon_cell(const BoxRec& B, const Geo& g, CProb* P, int i, int j, int k, double phi,
+                        unsigned long long& floors) {
+  const int x[3] = {i, j, k};
+  const int o = g.g(i, j, k), oh = g.h(i, j, k);
+  Stencil S;
+  double up[5], dn[5];
+  trace_load<D, false>(g, g.q(B.scr), o, S);
+  recon_eval<D, LIM>(P, S, phi, x[D], B.n[D], up, dn, floors);
+  trace_store<D>(B, g, oh, up, dn);
+  if (g.ns > 0) recon_species<D, LIM>(B, g, o, oh, phi);
+}
+
+template <int D, int LIM>
 __global__ __launch_bounds__(kBlock) void k_recon(const Segs L) {
   for_each_unit(L, [&](const March& M, const BoxRec& B) {
-    CProb* P = cprob(B.P);
     const Geo g(B.n, B.ns);
-    const gdbl* __restrict__ q = g.q(B.scr);
     const gdbl* __restrict__ phiv = g.phi(B.scr);
     unsigned long long floors = 0;
     march(kCells1, B, M, [&](int i, int j, int k) {
-      const int x[3] = {i, j, k};
-      const int o = g.g(i, j, k), oh = g.h(i, j, k);
-      const double phi = phiv[oh];
-      Stencil S;
-      double up[5], dn[5];
-      trace_load<D, false>(g, q, o, S);
-      recon_eval<D, LIM>(P, S, phi, x[D], B.n[D], up, dn, floors);
-      trace_store<D>(B, g, oh, up, dn);
-      if (g.ns > 0) recon_species<D, LIM>(B, g, o, oh, phi);
+      recon_cell<D, LIM>(B, g, cprob(B.P), i, j, k, phiv[g.h(i, j, k)], floors);
+    });
+    count(&B.P->cnt[2], floors);
+  });
+}
+
+// Flattening and face states for small sets: a third of the grid per
+// direction, as k_trace_dir.
+template <int LIM>
+__global__ __launch_bounds__(kBlock) void k_recon_dir(const Segs L) {
+  for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
+    const Geo g(B.n, B.ns);
+    CProb* P = cprob(B.P);
+    const gdbl* __restrict__ q = g.q(B.scr);
+    gdbl* __restrict__ phiout = g.phi(B.scr);
+    unsigned long long floors = 0;
+    march(kCells1, B, M, [&](int i, int j, int k) {
+      const double phi = flatten_cell(g, q, g.g(i, j, k));
+      if (d == 0) {
+        phiout[g.h(i, j, k)] = phi;
+        recon_cell<0, LIM>(B, g, P, i, j, k, phi, floors);
+      } else if (d == 1) {
+        recon_cell<1, LIM>(B, g, P, i, j, k, phi, floors);
+      } else {
+        recon_cell<2, LIM>(B, g, P, i, j, k, phi, floors);
+      }
     });
     count(&B.P->cnt[2], floors);
   });
@@ -1815,7 +1891,8 @@ const char* stage_name(int s) {
       "trace_x", "trace_y", "trace_z", "riemann_x", "riemann_y", "riemann_z",
       "trans1_x", "trans1_y", "trans1_z", "trans2_x", "trans2_y", "trans2_z", "update", "flip",
       "recon_x", "recon_y", "recon_z", "mol_update", "trace_xyz", "trans1_xyz", "recon_xyz", "species_xyz",
-      "riemann_xyz", "trans2_xyz", "mol_flux_update", "fill_cons2prim_cfl", "fill_cons2prim"};
+      "riemann_xyz", "trans2_xyz", "mol_flux_update", "fill_cons2prim_cfl", "fill_cons2prim",
+      "trace_dir", "trans1_dir", "recon_dir"};
   return (s >= 0 && s < kNumStages) ? names[s] : "?";
 }
 
@@ -1891,7 +1968,6 @@ hipError_t launch_stage(int stage, const Launch& L) {
         else k_spec3<0, true><<<grid, block, 0, s>>>(G);
       }
       break;
-#undef CTU_LIM3
     case kStT1All:
       if (L.sp) {
         if (L.rs) k_trans1_all<1, true><<<grid, block, 0, s>>>(G);
@@ -1914,6 +1990,9 @@ hipError_t launch_stage(int stage, const Launch& L) {
     case kStT2Z: CTU_RS(k_trans2, 2); break;
     case kStRiem3: CTU_RS3(k_riemann3); break;
     case kStT2All: CTU_RS3(k_trans2_3); break;
+    case kStT1Dir: CTU_RS3(k_trans1_dir); break;
+    case kStTraceDir: CTU_LIM3(k_trace_dir); break;
+    case kStReconDir: CTU_LIM3(k_recon_dir); break;
 #undef CTU_RS3
 #undef CTU_RS
     case kStUpdate: 
@@ -1923,6 +2002,7 @@ hipError_t launch_stage(int stage, const Launch& L) {
     default: return hipErrorInvalidValue;
   }
 #undef CTU_LIM
+#undef CTU_LIM3
   return hipGetLastError();
 }
 

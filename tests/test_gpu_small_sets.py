@@ -84,3 +84,26 @@ def test_many_small_problems_in_one_set(ctx):
         ref, dts, _ = oracle.run_problem(p, 3)
         assert np.array_equal(s.state(), ref) and s.dt() == dts[-1]
         s.close()
+
+
+@pytest.mark.parametrize("n,box", [
+    ((62, 62, 49), (62, 62, 49)),   # 816 units of 256 cells with a halo of one: blocks of one direction
+    ((62, 62, 50), (62, 62, 50)),   # 832: the last set that takes them
+    ((62, 62, 51), (62, 62, 51)),   # 848: one kernel for the three directions
+    ((13, 4, 5), (13, 4, 5)),       # one part of a block a plane (a mirror image needs four cells of domain)
+    ((14, 14, 9), (5, 14, 2)),
+])
+@pytest.mark.parametrize("scheme,riemann,limiter,steepen,nspec", [
+    (0, 0, 0, 0, 2), (0, 1, 1, 0, 0), (0, 0, 0, 1, 0), (1, 0, 1, 0, 1), (2, 1, 0, 0, 0),
+])
+def test_blocks_of_one_direction(ctx, n, box, scheme, riemann, limiter, steepen, nspec):
+    prob = W.kelvin_helmholtz(n=n, box=box, seed=11, nspec=nspec)
+    prob.scheme, prob.riemann, prob.limiter, prob.steepen = scheme, riemann, limiter, steepen
+    prob.bc_lo, prob.bc_hi = (W.BC_OUTFLOW, W.BC_REFLECT, W.BC_REFLECT), (W.BC_REFLECT, W.BC_OUTFLOW, W.BC_REFLECT)
+    got = _step(ctx, prob, "batched", 1, 2)
+    split = _step(ctx, prob, "batched", 0, 2)
+    for a, b in zip(got, split):
+        assert np.array_equal(a, b, equal_nan=True)
+    if prob.zones < 10000:
+        ref, dts, _ = oracle.run_problem(prob, 2)
+        assert np.array_equal(got[0], ref) and got[2][0] == dts[-1]
