@@ -12,6 +12,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -34,6 +35,19 @@ constexpr int kFormStatic = 4;    // internal form of ctuppm_step_static: batche
 constexpr int kMaxProblems = 4096;  // host-mapped rejection flags per context
 constexpr int kMaxRetryDepth = 3;   // ctuppm_step_checked halves a rejected step at most this often
 
+// Sets of at most this many update units are bound by their launches, and take
+// fewer: dt and the commit in the last blocks of the conversion and the update
+// (a 32^3 box: 5 us less each), and ghost fill, boundaries and conversion
+// together where every ghost cell maps to a valid one (KH 100x77x61, 1835
+// units: 72 -> 53 us; a 32^3 box with outflow along x, step 63 -> 51; serving
+// mix of ten problems, 19000 units: 154 -> 165 us).
+constexpr int kFinUnits = 2048;
+// Sets of at most this many stage-1 units leave CUs idle and take tracing and
+// stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
+// us, 32^3 55 -> 50, 48^3 (500 units) 85.6 -> 84.5, 56^3 (812) 127 -> 120; 27
+// boxes of 16^3 (972) 121 -> 123, 72^3 (1628) 220 -> 221.
+constexpr int kDirUnits = 832;
+
 struct Level {
   std::vector<ctuppm_box> boxes;
   std::vector<double*> Ua, Ub;
@@ -54,7 +68,10 @@ struct LevelTables {
   FillTag* ftags = nullptr;
   Chunk* fch = nullptr;
   std::vector<int> fpre;
-  long long fcells = 0;  // ghost cells the copy tags fill
+  FillTag* gtags = nullptr;  // ghost tags of small levels (copies and boundaries), their chunks
+  Chunk* gch = nullptr;
+  int ngch = 0;
+  bool ghosts_mapped = false;  // they cover every ghost cell
   BcTag* btags[3] = {};
   Chunk* bch[3] = {};
   std::vector<int> bpre[3];
@@ -131,7 +148,7 @@ struct StepSet {
   int limiter = 0;  // likewise (reconstruction variant: 0 CW84, 1 CS, 2 CW84 + steepening)
   int species = 0;  // 1 when a problem of the set carries passive species
   int nboxes = 0;
-  int copies = 0;   // ghost fill and conversion in one launch: fin, and every ghost cell is a copy of a valid cell
+  int copies = 0;   // ghost fill, boundaries and conversion in one launch
   int dirs = 0;     // tracing and stage 1 by blocks of one direction each
   int fin = 0;      // dt and the commit by the last blocks of the conversion and the update
   int zvar = 0;     // work-unit variant of its launches (LevelTables)
@@ -346,19 +363,6 @@ void march_region(std::vector<March>& out, int box, const int org[3], const int 
     }
   }
 }
-
-// Sets of at most this many update units are bound by their launches, and take
-// fewer: dt and the commit in the last blocks of the conversion and the update
-// (a 32^3 box: 5 us less each), and, where every ghost cell is a copy, ghost
-// fill and conversion together (KH 100x77x61, 1835 units: 72 -> 53 us; serving
-// mix of ten problems, 19000 units: 154 -> 165 us).
-constexpr int kFinUnits = 2048;
-
-// Sets of at most this many stage-1 units leave CUs idle and take tracing and
-// stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
-// us, 32^3 55 -> 50, 48^3 (500 units) 85.6 -> 84.5, 56^3 (812) 127 -> 120; 27
-// boxes of 16^3 (972) 121 -> 123, 72^3 (1628) 220 -> 221.
-constexpr int kDirUnits = 832;
 
 constexpr int kMinUnitsPerCu = 8;  // deeper work units only while a level keeps this many per CU
 
@@ -600,8 +604,8 @@ int run_probs(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool flip, int guard) {
   return go();
 }
 
-// Ghost fill and conversion of every box of a set whose ghost cells are all
-// copies (with the CFL reduction, and dt if the set takes it there).
+// Ghost fill, boundaries and conversion of every box of a set whose ghost
+// cells are all mapped (with the CFL reduction and dt).
 int run_fill_c2p(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool cfl, bool timed, const StageArgs& A) {
   const int rf = rec_form(S->form);
   Segs G{}, T{};
@@ -620,8 +624,8 @@ int run_fill_c2p(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool cfl, bool timed,
     ProbDev* rec = level_rec(P, S->level);
     G.s[G.n] = Seg{L.recs[rf], L.units[S->zvar][kValid], nullptr, rec};
     G.beg[G.n + 1] = G.beg[G.n] + L.upre[S->zvar][kValid].back();
-    T.s[G.n] = Seg{L.recs[rf], L.fch, L.ftags, rec};
-    T.beg[G.n + 1] = T.beg[G.n] + L.fpre.back();
+    T.s[G.n] = Seg{L.recs[rf], L.gch, L.gtags, rec};
+    T.beg[G.n + 1] = T.beg[G.n] + L.ngch;
     T.n = G.n += 1;
   }
   return go();
@@ -789,15 +793,7 @@ void bc_tags(const Problem* P, int l, int d, std::vector<BcTag>& bt, std::vector
   const int nb = int(B.size());
   int dlo[3], dhi[3];
   level_domain(P->prm, l, dlo, dhi);
-  const double rgm1 = 1.0 / (P->prm.gamma - 1.0);
-  const double* s = P->prm.inflow;
-  double inflow_cons[kMaxV];
-  inflow_cons[0] = s[0];
-  inflow_cons[1] = s[0] * s[1];
-  inflow_cons[2] = s[0] * s[2];
-  inflow_cons[3] = s[0] * s[3];
-  inflow_cons[4] = s[4] * rgm1 + 0.5 * s[0] * ((s[1] * s[1] + s[2] * s[2]) + s[3] * s[3]);
-  for (int sp = 0; sp < P->prm.nspec; ++sp) inflow_cons[kNV + sp] = s[0] * P->prm.inflow_X[sp];
+  const double* inflow_cons = P->tmpl[0].inflow;
   bt.clear();
   bch.clear();
   bpre.assign(nb + 1, 0);
@@ -833,6 +829,134 @@ void bc_tags(const Problem* P, int l, int d, std::vector<BcTag>& bt, std::vector
     }
     bpre[b + 1] = int(bch.size());
   }
+}
+
+// Ghost tags of a small level: every ghost cell of a box mapped straight to a
+// valid cell (or the inflow state), as the same-level copies and then the
+// boundaries along x, y and z leave it.  Beyond the domain along several
+// directions a cell takes the last one's image of the one before it, so the
+// maps compose; an inflow boundary fixes the state, and reflecting ones after it
+// still negate their momentum.  *mapped: they cover every ghost cell (not when
+// boxes leave part of the domain bare, or a mirror image falls outside it).
+// gt and gch hold the level's copy tags and get the rest.
+void ghost_tags(const Problem* P, int l, std::vector<FillTag>& gt, std::vector<Chunk>& gch, bool* mapped) {
+  *mapped = false;
+  const auto& B = P->lev[l].boxes;
+  long long units = 0, ghosts = 0;
+  for (const auto& b : B) {
+    const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
+    units += (long long)((n[0] * n[1] + kBlock - 1) / kBlock) * n[2];
+    ghosts += grown_cells(n) - box_vol(b);
+  }
+  if (units > kFinUnits || P->nlevels != 1) {
+    gt.clear();
+    gch.clear();
+    return;
+  }
+  int dlo[3], dhi[3];
+  level_domain(P->prm, l, dlo, dhi);
+  const int* bc[2] = {P->prm.bc_lo, P->prm.bc_hi};
+  std::vector<std::array<int, 3>> images;  // shifts of a source box to its periodic images
+  for (int im = 0; im < 27; ++im) {
+    const int step[3] = {im % 3 - 1, im / 3 % 3 - 1, im / 9 - 1};
+    std::array<int, 3> sh{};
+    bool ok = true;
+    for (int d = 0; d < 3; ++d) {
+      ok = ok && (!step[d] || bc[0][d] == CTUPPM_BC_PERIODIC);
+      sh[d] = step[d] * (dhi[d] - dlo[d] + 1);
+    }
+    if (ok) images.push_back(sh);
+  }
+  for (int db = 0; db < int(B.size()); ++db)
+    for (int cat = 0; cat < 27; ++cat) {
+      const int side[3] = {cat % 3, cat / 3 % 3, cat / 9};  // 0 inside, 1 below, 2 above the domain
+      if (cat == 0) continue;
+      int lo[3], hi[3], slo[3], shi[3], how[3], neg = 0;
+      bool fixed = false, any = true;
+      for (int d = 0; d < 3; ++d) {
+        const bool periodic = bc[0][d] == CTUPPM_BC_PERIODIC;
+        lo[d] = B[db].lo[d] - kNG;
+        hi[d] = B[db].hi[d] + kNG;
+        if (side[d] == 1) hi[d] = std::min(hi[d], dlo[d] - 1);
+        if (side[d] == 2) lo[d] = std::max(lo[d], dhi[d] + 1);
+        if (side[d] == 0 && !periodic) {
+          lo[d] = std::max(lo[d], dlo[d]);
+          hi[d] = std::min(hi[d], dhi[d]);
+        }
+        any = any && lo[d] <= hi[d] && !(side[d] && periodic);
+        // the source range of the cells lo..hi
+        how[d] = kMapShift;
+        slo[d] = lo[d];
+        shi[d] = hi[d];
+        if (!side[d] || !any) continue;
+        const int kind = bc[side[d] - 1][d], edge = side[d] == 1 ? dlo[d] : dhi[d];
+        if (kind == CTUPPM_BC_INFLOW) {
+          fixed = true;
+          neg = 0;
+        } else if (kind == CTUPPM_BC_OUTFLOW) {
+          how[d] = kMapClamp;
+          slo[d] = shi[d] = edge;
+        } else {
+          how[d] = kMapMirror;
+          neg ^= kMapNegate << d;
+          const int twice = 2 * edge + (side[d] == 1 ? -1 : 1);
+          slo[d] = twice - hi[d];
+          shi[d] = twice - lo[d];
+        }
+      }
+      if (!any) continue;
+      auto put = [&](int src, const int clo[3], const int chi[3], const int off[3], int mode) {
+        FillTag t{};
+        t.dst = db;
+        t.src = src;
+        for (int d = 0; d < 3; ++d) {
+          t.lo[d] = clo[d] - B[db].lo[d];
+          t.ext[d] = chi[d] - clo[d] + 1;
+          t.off[d] = off[d];
+        }
+        t.mode = mode;
+        chunk_region(gch, int(gt.size()), (long long)t.ext[0] * t.ext[1] * t.ext[2]);
+        gt.push_back(t);
+      };
+      if (fixed) {
+        const int off[3] = {0, 0, 0};
+        put(db, lo, hi, off, neg | kMapInflow | kMapClamp | kMapClamp << 2 | kMapClamp << 4);
+        continue;
+      }
+      for (int sb = 0; sb < int(B.size()); ++sb)
+        for (const auto& sh : images) {
+          int blo[3], bhi[3], rlo[3], rhi[3], clo[3], chi[3], off[3], mode = neg;
+          for (int d = 0; d < 3; ++d) {
+            blo[d] = B[sb].lo[d] + sh[d];
+            bhi[d] = B[sb].hi[d] + sh[d];
+          }
+          if (!intersect(slo, shi, blo, bhi, rlo, rhi)) continue;
+          for (int d = 0; d < 3; ++d) {  // the cells whose sources are rlo..rhi, and the map in local indices
+            mode |= how[d] << (2 * d);
+            if (how[d] == kMapShift) {
+              clo[d] = rlo[d];
+              chi[d] = rhi[d];
+              off[d] = B[db].lo[d] - blo[d];
+            } else if (how[d] == kMapClamp) {
+              clo[d] = lo[d];
+              chi[d] = hi[d];
+              off[d] = rlo[d] - blo[d];
+            } else {
+              const int twice = slo[d] + hi[d];
+              clo[d] = twice - rhi[d];
+              chi[d] = twice - rlo[d];
+              off[d] = twice - B[db].lo[d] - blo[d];
+            }
+          }
+          put(sb, clo, chi, off, mode);
+        }
+    }
+  long long cells = 0;
+  for (const auto& t : gt) cells += (long long)t.ext[0] * t.ext[1] * t.ext[2];
+  *mapped = cells == ghosts;
+  if (*mapped) return;
+  gt.clear();
+  gch.clear();
 }
 
 // Host tables of a two-level problem (box indices local to each level).
@@ -1011,6 +1135,9 @@ void meta_bytes(ctuppm_ctx* c, Problem* P) {
     std::vector<int> pre;
     fill_tags(P, l, ft, fch, pre);
     t += packed<FillTag>((long long)ft.size()) + packed<Chunk>((long long)fch.size());
+    bool mapped;
+    ghost_tags(P, l, ft, fch, &mapped);
+    t += packed<FillTag>((long long)ft.size()) + packed<Chunk>((long long)fch.size());
     for (int d = 0; d < 3; ++d) {
       std::vector<BcTag> bt;
       std::vector<Chunk> bch;
@@ -1115,8 +1242,6 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
     std::vector<FillTag> ft;
     std::vector<Chunk> fch;
     fill_tags(P, l, ft, fch, T.fpre);
-    T.fcells = 0;
-    for (const auto& t : ft) T.fcells += (long long)t.ext[0] * t.ext[1] * t.ext[2];
     T.ftags = K.put(ft);
     T.fch = K.put(fch);
     for (int d = 0; d < 3; ++d) {
@@ -1126,6 +1251,10 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
       T.btags[d] = K.put(bt);
       T.bch[d] = K.put(bch);
     }
+    ghost_tags(P, l, ft, fch, &T.ghosts_mapped);
+    T.gtags = K.put(ft);
+    T.gch = K.put(fch);
+    T.ngch = int(fch.size());
   }
   if (P->nlevels == 2) {
     TwoHost H;
@@ -1231,21 +1360,18 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   long long deep = 0;
   for (Problem* P : S->probs) deep += P->lt[level].upre[0][kCells1T].back();
   S->zvar = S->form == CTUPPM_FORM_PER_BOX ? 1 : (deep < (long long)kMinUnitsPerCu * c->num_cus ? 2 : 0);
-  long long upd = 0, ghosts = 0, cells1 = 0;
+  long long upd = 0, cells1 = 0;
+  bool mapped = true;
   for (Problem* P : S->probs) {
     const LevelTables& T = P->lt[level];
     upd += T.upre[S->zvar][kValid].back();
     cells1 += T.upre[S->zvar][kCells1].back();
-    ghosts -= T.fcells;
-    for (const auto& b : P->lev[level].boxes) {
-      const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
-      ghosts += grown_cells(n) - box_vol(b);
-    }
+    mapped = mapped && T.ghosts_mapped;
   }
   S->fin = upd <= kFinUnits && (S->form != CTUPPM_FORM_PER_BOX || S->nboxes == 1) && S->form != CTUPPM_FORM_WAVES &&
            S->probs[0]->nlevels == 1;
   S->dirs = S->fin && cells1 <= kDirUnits;
-  S->copies = S->fin && ghosts == 0;
+  S->copies = S->fin && mapped;
   *out = S.get();
   c->sets[key] = std::move(S);
   return CTUPPM_OK;
@@ -1845,6 +1971,13 @@ int ctuppm_problem_create(ctuppm_ctx* c, const ctuppm_params* prm, int nlevels, 
     h.dx[d] = prm->dx[d];
     h.rdx[d] = 1.0 / prm->dx[d];
   }
+  const double* in = prm->inflow;
+  h.inflow[0] = in[0];
+  h.inflow[1] = in[0] * in[1];
+  h.inflow[2] = in[0] * in[2];
+  h.inflow[3] = in[0] * in[3];
+  h.inflow[4] = in[4] * h.rgm1 + 0.5 * in[0] * ((in[1] * in[1] + in[2] * in[2]) + in[3] * in[3]);
+  for (int s = 0; s < prm->nspec; ++s) h.inflow[kNV + s] = in[0] * prm->inflow_X[s];
   h.nlevels = nlevels;
   h.nspec = prm->nspec;
   h.scheme = prm->scheme;

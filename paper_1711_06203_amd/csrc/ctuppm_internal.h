@@ -73,6 +73,7 @@ struct ProbDev {
   unsigned long long fail_mark;    // failure count [4] when the last step was committed or rejected
   int* hflag;                      // host-mapped copy of `rejected` (read by the host without a sync)
   int pad5[2];
+  double inflow[kMaxV];            // conserved inflow state
   // running max of the signal speed as bit patterns (>= 0), one 128-byte
   // line per slot so blocks of one launch do not contend on one address
   unsigned long long smax[kSlots][16];
@@ -120,7 +121,13 @@ struct Segs {
 };
 
 // Same-level ghost copy: dst-local cells [lo, lo+ext) <- src-local (cell + off).
-struct FillTag { int dst, src; int lo[3]; int ext[3]; int off[3]; int pad; };
+// The ghost tags of small sets also go through physical boundaries: mode holds,
+// per direction d in bits 2d and 2d + 1, how the source index follows from the
+// cell's (shifted by off, off itself, or off less the cell's), then per
+// direction whether the momentum is negated, then whether the source is the
+// inflow state instead.
+struct FillTag { int dst, src; int lo[3]; int ext[3]; int off[3]; int mode; };
+enum Map : int { kMapShift = 0, kMapClamp = 1, kMapMirror = 2, kMapNegate = 1 << 6, kMapInflow = 1 << 9 };
 // Physical boundary along dir on one side of the domain, over a box's grown cells.
 struct BcTag { int box; int dir; int side; int bc; int lo[3]; int ext[3]; int dom_lo, dom_hi; double inflow[kMaxV]; };
 

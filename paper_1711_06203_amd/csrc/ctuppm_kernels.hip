@@ -406,12 +406,13 @@ __global__ __launch_bounds__(kBlock) void k_c2p(const Segs L, int arr) {
   c2p_units<WQ, CFL, FIN, WQ ? kGrown : kValid>(L, arr, blockIdx.x, gridDim.x, lds);
 }
 
-// Ghost fill and conversion in one launch, for small sets all of whose ghost
-// cells are copies of valid cells (periodic domains): the first blocks convert
-// the valid cells, the others take the copy tags T, storing each source cell's
-// state to the ghost cell and its primitives to q, so neither waits for the
-// other.  One 48^3 box 20.5 -> 11.7 us; at 256^3 it would take 0.84 ms against
-// 0.60 for the two launches, whose conversion writes whole rows of q.
+// Ghost fill, physical boundaries and conversion in one launch, for small
+// sets: the first blocks convert the valid cells, the others take the ghost
+// tags T, each of which maps its cells straight to valid ones (through the
+// boundaries of every direction they lie beyond) or to the inflow state,
+// storing the ghost cell's state and its primitives, so nothing waits for
+// anything else.  One 48^3 periodic box 20.5 -> 11.7 us; at 256^3 it would take
+// 0.84 ms against 0.60 for fill and conversion, which write whole rows of q.
 template <bool CFL>
 __global__ __launch_bounds__(kBlock) void k_fill_c2p(const Segs L, const Segs T, int vblocks, int arr) {
   __shared__ double lds[kBlock / 64];
@@ -430,21 +431,33 @@ __global__ __launch_bounds__(kBlock) void k_fill_c2p(const Segs L, const Segs T,
     const BoxRec& D = S.boxes[G.dst];
     const BoxRec& Sb = S.boxes[G.src];
     const Geo gd(D.n, D.ns), gs(Sb.n, Sb.ns);
-    const gdbl* __restrict__ src = gp(state_arr(Sb, arr)) + gs.g(i + G.off[0], j + G.off[1], k + G.off[2]);
+    const int x[3] = {i, j, k};
+    int y[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const int how = G.mode >> (2 * d) & 3;
+      y[d] = how == kMapShift ? G.off[d] + x[d] : (how == kMapMirror ? G.off[d] - x[d] : G.off[d]);
+    }
+    CProb* P = cprob(D.P);
+    const bool fixed = G.mode & kMapInflow;
+    const gdbl* __restrict__ src = gp(state_arr(Sb, arr)) + gs.g(y[0], y[1], y[2]);
     const int di = gd.g(i, j, k);
     gdbl* __restrict__ dst = gp(state_arr(D, arr)) + di;
     double v[5];
 #pragma unroll
-    for (int m = 0; m < kNV; ++m) v[m] = src[m * gs.gcomp];
+    for (int m = 0; m < kNV; ++m) {
+      v[m] = fixed ? P->inflow[m] : src[m * gs.gcomp];
+      if (m >= 1 && m <= 3 && (G.mode & (kMapNegate << (m - 1)))) v[m] = -v[m];
+    }
 #pragma unroll
     for (int m = 0; m < kNV; ++m) dst[m * gd.gcomp] = v[m];
     unsigned long long hd = 0, hp = 0;
     prim_cell<true, false>(
-        cprob(D.P), gd, gd.q(D.scr), di, v[0], v[1], v[2], v[3], v[4],
+        P, gd, gd.q(D.scr), di, v[0], v[1], v[2], v[3], v[4],
         [&](int is) {
-          const double x = src[(kNV + is) * gs.gcomp];
-          dst[(kNV + is) * gd.gcomp] = x;
-          return x;
+          const double xs = fixed ? P->inflow[kNV + is] : src[(kNV + is) * gs.gcomp];
+          dst[(kNV + is) * gd.gcomp] = xs;
+          return xs;
         },
         hd, hp);
     count(&D.P->cnt[0], hd);

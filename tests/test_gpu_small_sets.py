@@ -1,5 +1,6 @@
 """Small sets take dt and the commit in the last blocks of the conversion and
-the update, and periodic ones their ghost fill in the conversion's launch.
+the update, and their ghost fill, through the boundaries too, in the
+conversion's launch.
 Each value takes the same operations as in the launches of their own that
 larger sets use, so states, ghost cells, dt and counters are compared bit for
 bit, with the oracle and with the split stages."""
@@ -107,3 +108,32 @@ def test_blocks_of_one_direction(ctx, n, box, scheme, riemann, limiter, steepen,
     if prob.zones < 10000:
         ref, dts, _ = oracle.run_problem(prob, 2)
         assert np.array_equal(got[0], ref) and got[2][0] == dts[-1]
+
+
+P, O, R, I = W.BC_PERIODIC, W.BC_OUTFLOW, W.BC_REFLECT, W.BC_INFLOW
+
+
+@pytest.mark.parametrize("form", ["per_box", "batched", "graph"])
+@pytest.mark.parametrize("n,box", [
+    ((12, 10, 9), (12, 10, 9)),      # one box: every ghost cell an image of its own
+    ((12, 10, 9), (5, 4, 9)),        # images that lie in other boxes
+    ((12, 10, 9), (1, 3, 2)),        # boxes thinner than the ghost layers, some beside the walls
+    ((4, 5, 4), (3, 5, 2)),          # the smallest domain a mirror image fits
+])
+@pytest.mark.parametrize("bc_lo,bc_hi", [
+    ((O, O, O), (O, O, O)), ((R, R, R), (R, R, R)), ((I, I, I), (I, I, I)),
+    ((O, P, P), (O, P, P)), ((P, P, R), (P, P, R)),
+    ((R, I, O), (I, O, R)), ((I, R, P), (R, O, P)), ((O, R, I), (I, I, R)), ((R, P, I), (O, P, R)),
+])
+def test_ghost_cells_through_boundaries(ctx, form, n, box, bc_lo, bc_hi):
+    """Edge and corner ghost cells too: U^n with its ghost cells is compared."""
+    scheme = sum(bc_lo) % 3
+    prob = W.kelvin_helmholtz(n=n, box=box, seed=n[0] + box[0], nspec=2)
+    prob.scheme, prob.bc_lo, prob.bc_hi = scheme, bc_lo, bc_hi
+    prob.inflow, prob.inflow_X = (1.25, 0.5, -0.25, 0.125, 2.0), (0.25, 0.75)
+    got = _step(ctx, prob, form, 1, 2)
+    split = _step(ctx, prob, form, 0, 2)
+    ref, dts, _ = oracle.run_problem(prob, 2)
+    assert np.array_equal(got[0], ref) and got[2][0] == dts[-1]
+    for a, b in zip(got, split):
+        assert np.array_equal(a, b, equal_nan=True)
