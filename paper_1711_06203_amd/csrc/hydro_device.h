@@ -25,6 +25,8 @@ CTU_DEV double dmax(double a, double b) { return a > b ? a : b; }
 // needed, so a wave skips it instead of computing and discarding it.
 CTU_DEV bool any_lane(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
 
+CTU_DEV bool same_bits(double a, double b) { return __double_as_longlong(a) == __double_as_longlong(b); }
+
 // Monotonised-central slope of the middle of three cell values.
 CTU_DEV double mc_slope(double am, double a0, double ap) {
   const double dm = a0 - am, dp = ap - a0, dc = 0.5 * (ap - am);
@@ -307,7 +309,11 @@ CTU_DEV void hllc(const double L[5], const double R[5], double g, double rgm1, d
 // speeds W(p) = C sqrt(1 + (gamma+1)/(2 gamma) (p/p_K - 1)); the star
 // pressure from the acoustic estimate by a fixed number of Newton steps on
 // u*_L(p) = u*_R(p) with curve slopes Z = 2 W^3 / (W^2 + C^2), floored; the
-// contact speed from the last W.  The state at x/t = 0 is on the contact's
+// contact speed from the last W.  A step depends on the pressure alone, so once
+// it returns the pressure it started from, or the one before that (the last
+// bits alternate), every later one is known; a wave stops there with the value
+// of the last step.  (Shock tube of 96^3: normal fluxes 141 -> 105 us,
+// stage 1 300 -> 229, final fluxes 185 -> 160.)  The state at x/t = 0 is on the contact's
 // upwind side K: K beyond the K wave, the star state (density from the shock
 // relation) behind it, a linear blend inside a rarefaction fan that straddles
 // x/t = 0; transverse velocities (and species, through W) from K.
@@ -321,7 +327,9 @@ CTU_DEV void twoshock(const double L[5], const double R[5], double g, double rgm
   const double CL = sqrt(g * pL * rL), CR = sqrt(g * pR * rR);
   double ps = ((CR * pL + CL * pR) + CL * CR * (uL - uR)) / (CL + CR);
   ps = dmax(ps, sp);
-  double WL = CL, WR = CR;
+  double WL = CL, WR = CR, before = ps;
+  bool stale = true;  // WL, WR are not those of ps
+#pragma unroll 1
   for (int it = 0; it < kTwoShockIters; ++it) {
     WL = CL * sqrt(1.0 + gp * (ps / pL - 1.0));
     WR = CR * sqrt(1.0 + gp * (ps / pR - 1.0));
@@ -329,11 +337,21 @@ CTU_DEV void twoshock(const double L[5], const double R[5], double g, double rgm
     const double ZR = 2.0 * (WR * WR * WR) / (WR * WR + CR * CR);
     const double usL = uL - (ps - pL) / WL;
     const double usR = uR + (ps - pR) / WR;
-    ps = ps - (ZL * ZR) * (usR - usL) / (ZL + ZR);
-    ps = dmax(ps, sp);
+    const double p = dmax(ps - (ZL * ZR) * (usR - usL) / (ZL + ZR), sp);
+    const bool fixed = same_bits(p, ps), back = it > 0 && same_bits(p, before);
+    const bool odd = (kTwoShockIters - 1 - it) & 1;  // steps left
+    if (!any_lane(!(fixed || back))) {
+      stale = !(fixed || odd);
+      ps = odd ? ps : p;
+      break;
+    }
+    before = ps;
+    ps = p;
   }
-  WL = CL * sqrt(1.0 + gp * (ps / pL - 1.0));
-  WR = CR * sqrt(1.0 + gp * (ps / pR - 1.0));
+  if (any_lane(stale)) {
+    WL = CL * sqrt(1.0 + gp * (ps / pL - 1.0));
+    WR = CR * sqrt(1.0 + gp * (ps / pR - 1.0));
+  }
   const double us = ((WL * uL + WR * uR) + (pL - pR)) / (WL + WR);
   const bool left = us >= 0.0;
   const double WK = left ? WL : WR;
