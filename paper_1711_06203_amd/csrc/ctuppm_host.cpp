@@ -42,6 +42,11 @@ constexpr int kMaxRetryDepth = 3;   // ctuppm_step_checked halves a rejected ste
 // units: 72 -> 53 us; a 32^3 box with outflow along x, step 63 -> 51; serving
 // mix of ten problems, 19000 units: 154 -> 165 us).
 constexpr int kFinUnits = 2048;
+// That one launch pays up to twice as many units while boxes grown by their
+// ghost cells hold at most this many cells (96^3 step, one box 485.6 -> 480.5
+// us, boxes of 48^3 655 -> 642; 27 boxes of 32^3, 1.73 M cells: 931 -> 941,
+// 216 of 16^3, 2.99 M: 1135 -> 1182 by the third-order method of lines).
+constexpr long long kMapCells = 1600000;
 // Sets of at most this many stage-1 units leave CUs idle and take tracing and
 // stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
 // us, 32^3 55 -> 50, 48^3 (500 units) 85.6 -> 84.5, 56^3 (812) 127 -> 120; 27
@@ -842,13 +847,14 @@ void bc_tags(const Problem* P, int l, int d, std::vector<BcTag>& bt, std::vector
 void ghost_tags(const Problem* P, int l, std::vector<FillTag>& gt, std::vector<Chunk>& gch, bool* mapped) {
   *mapped = false;
   const auto& B = P->lev[l].boxes;
-  long long units = 0, ghosts = 0;
+  long long units = 0, ghosts = 0, valid = 0;
   for (const auto& b : B) {
     const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
     units += (long long)((n[0] * n[1] + kBlock - 1) / kBlock) * n[2];
     ghosts += grown_cells(n) - box_vol(b);
+    valid += box_vol(b);
   }
-  if (units > kFinUnits || P->nlevels != 1) {
+  if (units > 2 * kFinUnits || ghosts + valid > kMapCells || P->nlevels != 1) {
     gt.clear();
     gch.clear();
     return;
@@ -1360,15 +1366,20 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   long long deep = 0;
   for (Problem* P : S->probs) deep += P->lt[level].upre[0][kCells1T].back();
   S->zvar = S->form == CTUPPM_FORM_PER_BOX ? 1 : (deep < (long long)kMinUnitsPerCu * c->num_cus ? 2 : 0);
-  long long upd = 0, cells1 = 0;
+  long long upd = 0, cells1 = 0, grown = 0;
   bool mapped = true;
   for (Problem* P : S->probs) {
     const LevelTables& T = P->lt[level];
     upd += T.upre[S->zvar][kValid].back();
     cells1 += T.upre[S->zvar][kCells1].back();
     mapped = mapped && T.ghosts_mapped;
+    for (const auto& b : P->lev[level].boxes) {
+      const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
+      grown += grown_cells(n);
+    }
   }
-  S->fin = upd <= kFinUnits && (S->form != CTUPPM_FORM_PER_BOX || S->nboxes == 1) && S->form != CTUPPM_FORM_WAVES &&
+  mapped = mapped && grown <= kMapCells;
+  S->fin = upd <= (mapped ? 2 : 1) * kFinUnits && (S->form != CTUPPM_FORM_PER_BOX || S->nboxes == 1) && S->form != CTUPPM_FORM_WAVES &&
            S->probs[0]->nlevels == 1;
   S->dirs = S->fin && cells1 <= kDirUnits;
   S->copies = S->fin && mapped;

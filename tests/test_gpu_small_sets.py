@@ -137,3 +137,19 @@ def test_ghost_cells_through_boundaries(ctx, form, n, box, bc_lo, bc_hi):
     assert np.array_equal(got[0], ref) and got[2][0] == dts[-1]
     for a, b in zip(got, split):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("n,box,nspec", [
+    ((101, 101, 93), (101, 101, 93), 0),    # 3720 update units, 1.2 M cells with ghosts: one launch
+    ((96, 96, 114), (96, 96, 114), 0),      # 4104 units: launches of their own
+    ((84, 72, 64), (16, 16, 16), 1),        # 1.42 M cells with ghosts in boxes of 16^3 and less
+    ((90, 80, 64), (16, 16, 16), 0),        # 1.59 M
+    ((96, 80, 64), (16, 16, 16), 0),        # 1.66 M: too many
+])
+def test_ghosts_with_conversion_at_the_edges_of_the_rule(ctx, n, box, nspec):
+    prob = W.kelvin_helmholtz(n=n, box=box, seed=5, nspec=nspec)
+    prob.bc_lo, prob.bc_hi = (O, P, R), (R, P, O)
+    got = _step(ctx, prob, "batched", 1, 1)
+    split = _step(ctx, prob, "batched", 0, 1)
+    for a, b in zip(got, split):
+        assert np.array_equal(a, b, equal_nan=True)
