@@ -153,3 +153,23 @@ def test_ghosts_with_conversion_at_the_edges_of_the_rule(ctx, n, box, nspec):
     split = _step(ctx, prob, "batched", 0, 1)
     for a, b in zip(got, split):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("bc", [O, R, I])
+def test_bare_parts_of_the_domain_keep_the_callers_ghosts(ctx, bc):
+    """Ghost cells over a part of the domain without boxes have no source: they
+    stay what the caller made them, and the set keeps its launches."""
+    from paper_1711_06203_amd import ctuppm
+    prob = W.kelvin_helmholtz(n=(18, 16, 12), box=(9, 8, 6), seed=2)
+    prob.boxes = prob.boxes[:-1]
+    prob.bc_lo, prob.bc_hi = (bc, O, P), (O, bc, P)
+    out = []
+    for fused in (1, 0):
+        ctx.set_fused(fused)
+        s = ctuppm.Solver(ctx, prob, form="batched")
+        s.UA[ctx.torch.isnan(s.UA) | (s.UA == 0.0)] = 0.125
+        s.step(2)
+        out.append((s.UA.cpu().numpy(), s.UB.cpu().numpy(), s.counters(), s.dt()))
+        s.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b, equal_nan=True)
