@@ -132,7 +132,10 @@ struct Problem {
   bool filled[2] = {false, false};   // ghosts of the level's current state filled since it last changed
   bool dt_ready = false;             // dt computed since the last advance
   bool averaged = false;             // fine level averaged down in this coarse step
-  int scratch_rf = -1;               // scratch layout (record form) the last advance left its arrays in, -1 none
+  // the last advance kept its normal fluxes out of memory: the scratch layout
+  // (record form) it left its face states in, -1 when they are in memory
+  int scratch_rf = -1;
+  int tab_wave = 0;                  // wave size the tables last uploaded were built for
   void state_changed() {
     filled[0] = filled[1] = false;
     dt_ready = false;
@@ -1169,6 +1172,46 @@ size_t meta_total(const Problem* P) { return P->rec_bytes + P->tab_bytes; }
 // the stage scratch, the two-level region and register.
 size_t scratch_base(const Problem* P) { return meta_total(P) + stage_fab_bytes(P->lev[0].boxes, P->prm); }
 
+// Whether a method-of-lines step of a set leaves the normal fluxes to the
+// update.  With species the update would read every species' z states twice
+// from memory (two planes of 18 components do not stay in an XCD's L2: KH 128^3
+// with 13 species 2.11 ms a step against 2.01 for the two kernels; without
+// species 1.10 against 1.73 ms at 160^3).
+bool flux_in_update(const ctuppm_ctx* c, const StepSet* S) { return S->scheme != 0 && c->fused && !S->species; }
+
+// The normal fluxes an advance kept out of memory, solved from the face states
+// it left in a scratch slot (the box's number in the batched forms, 0 in the
+// per-box form), for stage dumps.  The slot holds the box that used it last, by
+// the wave size of the advance (whose tables stand until they are rebuilt).
+// Nothing to do when the last advance stored its fluxes or used another layout.
+int recompute_fluxes(ctuppm_ctx* c, Problem* P, int slot, int rf) {
+  if (P->scratch_rf != rf) return CTUPPM_OK;
+  const auto& B = P->lev[0].boxes;
+  const int nb = int(B.size()), ns = P->prm.nspec;
+  const int slots = rf == 0 ? nb : (rf == 1 ? 1 : P->tab_wave);
+  if (slot >= slots) return CTUPPM_OK;  // no box has used it
+  const int b = slot + (nb - 1 - slot) / slots * slots;
+  size_t off = scratch_base(P);
+  if (rf == 0) {
+    for (int x = 0; x < b; ++x) off += box_scratch_bytes(B[x], ns);
+  } else {
+    size_t size = 0;
+    for (const auto& x : B) size = std::max(size, box_scratch_bytes(x, ns));
+    off += size_t(slot) * size;
+  }
+  // (a workspace bound again at the same address may be smaller than the step's)
+  if (off + box_scratch_bytes(B[b], ns) > P->ws_bytes)
+    return fail(c, CTUPPM_ENOMEM, "problem %d: the scratch of box %d ends at byte %zu of a %zu-byte workspace",
+                P->id, b, off + box_scratch_bytes(B[b], ns), P->ws_bytes);
+  const LevelTables& T = P->lt[0];
+  const int k = stage_region(kStRiem3);
+  const std::vector<int>& pre = T.upre[2][k];
+  SegRun R{c, c->stream, kStRiem3, false, false, StageArgs()};
+  R.A.rs = P->prm.riemann;
+  const int rc = R.add(T.recs[rf], T.units[2][k] + pre[b], nullptr, P->dP, pre[b + 1] - pre[b]);
+  return rc ? rc : R.flush();
+}
+
 // Build the problem's device tables for the current binding, tuning and wave
 // size, and upload them (asynchronously) into its workspace.
 int ensure_tables(ctuppm_ctx* c, Problem* P) {
@@ -1179,6 +1222,15 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
                 meta_total(P));
   for (int l = 0; l < P->nlevels; ++l)
     if (!P->lev[l].bound) return fail(c, CTUPPM_ESTATE, "problem %d: level %d state not bound", P->id, l);
+  if (P->scratch_rf == 2 && P->tab_wave != c->wave_boxes) {
+    // these tables will place the boxes in other slots: the fluxes a dump may
+    // still ask for are stored by the old ones first
+    for (int slot = 0; slot < std::min(P->tab_wave, int(P->lev[0].boxes.size())); ++slot) {
+      const int rc = recompute_fluxes(c, P, slot, 2);
+      if (rc && rc != CTUPPM_ENOMEM) return rc;
+    }
+    P->scratch_rf = -1;
+  }
   Packer K;
   K.dbase = (char*)P->ws + P->rec_bytes;
   const int ns = P->prm.nspec;
@@ -1302,6 +1354,7 @@ int ensure_tables(ctuppm_ctx* c, Problem* P) {
   int rc = upload(c, K.dbase, K.buf.data(), K.buf.size());
   if (rc) return rc;
   P->tables_ok = true;
+  P->tab_wave = c->wave_boxes;
   return CTUPPM_OK;
 }
 
@@ -1413,25 +1466,6 @@ std::vector<std::pair<int, int>> box_groups(const ctuppm_ctx* c, const StepSet* 
   return g;
 }
 
-// Recompute a stage of the box that last used `box`'s scratch in `form`, from
-// the arrays that box left there: for stage dumps of arrays a fused kernel
-// keeps out of memory.  Does nothing when the last advance used another layout.
-int recompute_stage(ctuppm_ctx* c, Problem* P, int level, int box, int form, int stage) {
-  const int rf = rec_form(form);
-  if (P->scratch_rf != rf || ensure_tables(c, P) != CTUPPM_OK) return CTUPPM_OK;
-  const int nb = int(P->lev[level].boxes.size());
-  int b = box;
-  if (form == CTUPPM_FORM_PER_BOX) b = nb - 1;
-  if (form == CTUPPM_FORM_WAVES) b += (nb - 1 - box) / c->wave_boxes * c->wave_boxes;
-  const LevelTables& T = P->lt[level];
-  const std::vector<int>& pre = T.upre[2][stage_region(stage)];
-  SegRun R{c, c->stream, stage, false, false, StageArgs()};
-  R.A.rs = P->prm.riemann;
-  const int rc = R.add(T.recs[rf], T.units[2][stage_region(stage)] + pre[b], nullptr, level_rec(P, level),
-                       pre[b + 1] - pre[b]);
-  return rc ? rc : R.flush();
-}
-
 // Ghost fill of the state array `arr` of every box of a set: same-level
 // copies, then the physical boundaries x, y, z (box by box in the per-box form).
 int fill_arr(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int arr) {
@@ -1459,12 +1493,8 @@ int enqueue_mol(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard)
   const bool per_box = S->form == CTUPPM_FORM_PER_BOX;
   const int nst = S->scheme == 1 ? 2 : 3;
   // face states: flattening and the three directions in one kernel (fused,
-  // the default) or one kernel each.  Without species the fused form leaves
-  // the normal fluxes to the update; with them the update would read every
-  // species' z states twice from memory (two planes of 18 components do not
-  // stay in an XCD's L2: KH 128^3 with 13 species 2.11 ms a step against 2.01
-  // for the two kernels; without species 1.10 against 1.73 ms at 160^3)
-  const bool fluxup = c->fused && !S->species;
+  // the default) or one kernel each
+  const bool fluxup = flux_in_update(c, S);
   static const std::vector<int> fused_up = {kStRecon3}, fused = {kStRecon3, kStSpec3, kStRiem3};
   static const std::vector<int> split = {kStFlatten, kStReconX, kStReconY, kStReconZ, kStRiemX, kStRiemY, kStRiemZ};
   static const std::vector<int> dirs_up = {kStReconDir}, dirs = {kStReconDir, kStRiem3};
@@ -1823,7 +1853,7 @@ int step_set(ctuppm_ctx* c, const std::vector<int>& v, int form, int guard) {
     P->cur ^= 1;
     P->steps += 1;
     if (guard) P->guarded = true;  // the mirror holds only if no step is rejected
-    P->scratch_rf = rec_form(S->form);
+    P->scratch_rf = flux_in_update(c, S) ? rec_form(S->form) : -1;
     P->state_changed();
   }
   return CTUPPM_OK;
@@ -2106,7 +2136,7 @@ int ctuppm_bind_workspace(ctuppm_ctx* c, int pid, void* ws, size_t bytes) {
       if (rc) return rc;
     }
   }
-  P->scratch_rf = -1;
+  if (old != ws) P->scratch_rf = -1;
   P->ws = ws;
   P->ws_bytes = bytes;
   P->dP = (ProbDev*)ws;
@@ -2652,8 +2682,9 @@ int ctuppm_debug_stage(ctuppm_ctx* c, int pid, int level, int box, int array, in
                 pid, array, box, form, end, P->ws_bytes);
   if (!out) return CTUPPM_OK;
   // the method of lines without species keeps its normal fluxes out of memory
-  if (array >= 8 && array <= 10 && P->prm.scheme != CTUPPM_SCHEME_CTU && ns == 0) {
-    const int rc = recompute_stage(c, P, level, box, form, kStRiem3);
+  if (array >= 8 && array <= 10) {
+    const int rf = rec_form(form);
+    const int rc = recompute_fluxes(c, P, rf == 0 ? box : (rf == 1 ? 0 : box % c->wave_boxes), rf);
     if (rc) return rc;
   }
   const double* src = (const double*)((const char*)P->ws + off) + first;
