@@ -359,8 +359,10 @@ CTU_DEV double prim_cell(CProb* P, const Geo& g, gdbl* __restrict__ q, int o, do
 // Primitives of the cells of a region (WQ: stored), and the signal speed of
 // the valid cells (CFL: reduced per problem by wave shuffles, LDS and a 64-bit
 // atomic max on the bit pattern; non-negative doubles order like unsigned
-// integers, so the max is exact and order-free).  FIN: the last block also
-// takes dt.
+// integers, so the max is exact and order-free).  Cells whose speed is NaN are
+// passed over, so the max does not depend on which thread meets them after
+// which other cell, and is the same by every route.  FIN: the last block
+// also takes dt.
 template <bool WQ, bool CFL, bool FIN, int REGION>
 CTU_DEV void c2p_units(const Segs& L, int arr, int block, int blocks, double* lds) {
   double smax = 0.0;
@@ -382,7 +384,7 @@ CTU_DEV void c2p_units(const Segs& L, int arr, int block, int blocks, double* ld
           cprob(P), g, q, o, U[o], U[g.gcomp + o], U[2 * g.gcomp + o], U[3 * g.gcomp + o], U[4 * g.gcomp + o],
           [&](int is) { return U[(kNV + is) * g.gcomp + o]; }, hd, hp);
       if (CFL && (REGION == kValid || (i >= 0 && i < B.n[0] && j >= 0 && j < B.n[1] && k >= 0 && k < B.n[2])))
-        smax = dmax(smax, sig);
+        smax = dmax(sig, smax);  // dmax(a NaN, b) is b
     });
     if (WQ) {
       count(&P->cnt[0], hd);
