@@ -35,6 +35,10 @@ constexpr int kFormStatic = 4;    // internal form of ctuppm_step_static: batche
 constexpr int kMaxProblems = 4096;  // host-mapped rejection flags per context
 constexpr int kMaxRetryDepth = 3;   // ctuppm_step_checked halves a rejected step at most this often
 
+// The limits below count a set's work in units of at most 256 cells of one plane
+// (plane_units), whatever the units its launches are tuned to: the stages a set
+// takes do not depend on the tuning.
+//
 // Sets of at most this many update units are bound by their launches, and take
 // fewer: dt and the commit in the last blocks of the conversion and the update
 // (a 32^3 box: 5 us less each), and ghost fill, boundaries and conversion
@@ -380,6 +384,14 @@ long long max_units(const int n[3], int kind) {
   int org[3], ext[3];
   region_of(kind, n, org, ext);
   return (long long)ext[1] * ext[2] * ((ext[0] + kBlock - 1) / kBlock);
+}
+
+// Units of one plane of a box region: the size the limits on small sets count.
+long long plane_units(const ctuppm_box& b, int kind) {
+  const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
+  int org[3], ext[3];
+  region_of(kind, n, org, ext);
+  return (long long)((ext[0] * ext[1] + kBlock - 1) / kBlock) * ext[2];
 }
 
 int grid_for(const ctuppm_ctx* c, int nchunks, bool persistent) {
@@ -853,7 +865,7 @@ void ghost_tags(const Problem* P, int l, std::vector<FillTag>& gt, std::vector<C
   long long units = 0, ghosts = 0, valid = 0;
   for (const auto& b : B) {
     const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
-    units += (long long)((n[0] * n[1] + kBlock - 1) / kBlock) * n[2];
+    units += plane_units(b, kValid);
     ghosts += grown_cells(n) - box_vol(b);
     valid += box_vol(b);
   }
@@ -1422,12 +1434,11 @@ int build_set(ctuppm_ctx* c, const std::vector<int>& pids, int form, StepSet** o
   long long upd = 0, cells1 = 0, grown = 0;
   bool mapped = true;
   for (Problem* P : S->probs) {
-    const LevelTables& T = P->lt[level];
-    upd += T.upre[S->zvar][kValid].back();
-    cells1 += T.upre[S->zvar][kCells1].back();
-    mapped = mapped && T.ghosts_mapped;
+    mapped = mapped && P->lt[level].ghosts_mapped;
     for (const auto& b : P->lev[level].boxes) {
       const int n[3] = {box_n(b, 0), box_n(b, 1), box_n(b, 2)};
+      upd += plane_units(b, kValid);
+      cells1 += plane_units(b, kCells1);
       grown += grown_cells(n);
     }
   }
