@@ -152,9 +152,12 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
         for g in groups:
             ctx.set_stage_planes(lead[g], p)
         trials[p] = _stage_ms(ctx, solvers, steps)
+    # a trial that ran other stages is not comparable: a stage missing from it is
+    # not a stage that took no time
+    alike = [p for p in trials if set(trials[p]) == set(start)]
     best: Dict[int, int] = {}
     for g, sts in groups.items():
-        best[g] = min(trials, key=lambda p: sum(trials[p].get(st, 0.0) for st in sts))
+        best[g] = min(alike, key=lambda p: sum(trials[p][st] for st in sts)) if alike else before[lead[g]]
     for g, p in best.items():
         ctx.set_stage_planes(lead[g], p)
     tuned = sum(_stage_ms(ctx, solvers, steps).values())
