@@ -450,7 +450,15 @@ int ctuppm_set_tuning2(ctuppm_ctx* ctx, int blocks_per_cu, int zseg_batched, int
  * one box each, keeps one plane, two for cons->prim, times zseg_per_box).
  * Stages that run over the same work region share the setting:
  * ctuppm_stage_planes returns the stage's setting and its group (stages with
- * equal groups share it).  Defaults: 2 for cons->prim, 4 for the merged
+ * equal groups share it).  The launches of one direction each share those of
+ * the kernels they stand for ("trace_dir" and "trace_xyz", "recon_dir" and
+ * "recon_xyz", "trans1_dir" and "trans1_xyz").  "riemann_xyz" and "trans2_xyz"
+ * take the settings of "riemann_x", "_y", "_z" and "trans2_x", "_y", "_z" for
+ * their three parts: setting one of the two sets its three, reading it gives
+ * the x one.  A stage that a set does not launch leaves its setting without
+ * effect there: the normal fluxes of the method of lines without species (part
+ * of "mol_flux_update", in the group of "update"), cons->prim where the ghost
+ * fill is merged with it ("fill_cons2prim_cfl" and "fill_cons2prim", likewise).  Defaults: 2 for cons->prim, 4 for the merged
  * tracing (and its species stage) and the merged method-of-lines face states,
  * 1 elsewhere.  Problems
  * stepped together whose merged-tracing work units at that depth would number

@@ -229,8 +229,8 @@ struct ctuppm_ctx {
   // waves forms, times their zseg:
   // cons->prim two (each thread converts two independent cells), the merged
   // tracing four (measured: 2.31 -> 2.13 ms at KH 256^3), the rest one
-  int region_planes[kNumRegions] = {1, 2, 1, 1, 1, 1, 1, 1, 1, 4, 1};
-  static_assert(kNumRegions == 11 && kGrown == 1 && kCells1T == 9, "one default per work region");
+  int region_planes[kNumRegions] = {1, 2, 1, 1, 1, 1, 1, 1, 1, 4};
+  static_assert(kNumRegions == 10 && kGrown == 1 && kCells1T == 9, "one default per work region");
   bool region_set[kNumRegions] = {};  // set by the caller: used as given (defaults adapt to the level size)
   int fused = 1;          // CTU cell stages: tracing and stage 1 of the three directions in one kernel each
   std::vector<Staging> staging;
@@ -489,17 +489,9 @@ struct StageArgs {
   int spstage = 0;
 };
 
-// Launch one stage over a segment list with optional timing.
-int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool persistent, bool timed,
-                const StageArgs& A, const Segs* tags = nullptr) {
-  if (G.n <= 0 || G.beg[G.n] <= 0) return CTUPPM_OK;
-  Launch L{};
-  L.segs = G;
-  L.grid = grid_for(c, G.beg[G.n], persistent);
-  // these visit their units once per direction
-  if (stage == kStRiem3 || stage == kStT2All || stage == kStTraceDir || stage == kStT1Dir ||
-      stage == kStReconDir)
-    L.grid *= 3;
+// Launch one stage, its work lists and grid given in L, with optional timing.
+int launch_lists(ctuppm_ctx* c, hipStream_t s, int stage, Launch& L, bool timed, const StageArgs& A,
+                 const Segs* tags = nullptr) {
   L.stream = s;
   L.arr = A.arr;
   L.out = A.out;
@@ -530,6 +522,18 @@ int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool per
   return CTUPPM_OK;
 }
 
+// Launch one stage over a segment list (tags: the copy tags of the merged fill).
+int launch_segs(ctuppm_ctx* c, hipStream_t s, int stage, const Segs& G, bool persistent, bool timed,
+                const StageArgs& A, const Segs* tags = nullptr) {
+  if (G.n <= 0 || G.beg[G.n] <= 0) return CTUPPM_OK;
+  Launch L{};
+  L.segs = G;
+  L.grid = grid_for(c, G.beg[G.n], persistent);
+  // these visit their units once per direction
+  if (stage == kStTraceDir || stage == kStT1Dir || stage == kStReconDir) L.grid *= 3;
+  return launch_lists(c, s, stage, L, timed, A, tags);
+}
+
 // Collects the segments of one stage, launching whenever kMaxSeg are full.
 struct SegRun {
   ctuppm_ctx* c;
@@ -556,6 +560,42 @@ struct SegRun {
   }
 };
 
+// Likewise for the launches that take a list per direction.
+struct DirRun {
+  ctuppm_ctx* c;
+  hipStream_t s;
+  int stage;
+  bool persistent, timed;
+  StageArgs A;
+  DirSegs G{};
+  // the units of boxes b0..b1-1 of a level's lists
+  int add(const LevelTables& T, int rf, int zv, int b0, int b1) {
+    if (G.n == kMaxSeg) {
+      const int rc = flush();
+      if (rc) return rc;
+    }
+    G.s[G.n].boxes = T.recs[rf];
+    for (int d = 0; d < 3; ++d) {
+      const int k = stage_region_dir(stage, d);
+      const std::vector<int>& pre = T.upre[zv][k];
+      G.s[G.n].work[d] = T.units[zv][k] + pre[b0];
+      G.beg[G.n + 1][d] = G.beg[G.n][d] + pre[b1] - pre[b0];
+    }
+    G.n += 1;
+    return CTUPPM_OK;
+  }
+  int flush() {
+    const int* end = G.beg[G.n];
+    const int most = std::max({end[0], end[1], end[2]});
+    if (most == 0) return CTUPPM_OK;
+    Launch L{};
+    L.dirs = G;
+    L.grid = 3 * grid_for(c, most, persistent);
+    G = DirSegs{};
+    return launch_lists(c, s, stage, L, timed, A);
+  }
+};
+
 int rec_form(int form) {
   return form == CTUPPM_FORM_PER_BOX ? 1 : (form == CTUPPM_FORM_WAVES ? 2 : (form == kFormStatic ? 3 : 0));
 }
@@ -578,6 +618,8 @@ int run_range(ctuppm_ctx* c, StepSet* S, hipStream_t s, int stage, int b0, int b
   R.A.mol = S->scheme != 0;
   R.A.spstage = spstage;
   const int rf = rec_form(S->form), zv = S->zvar;
+  const bool lists = stage_by_lists(stage);
+  DirRun D{c, s, stage, R.persistent, timed, R.A};
   for (size_t ip = 0; ip < S->probs.size(); ++ip) {
     const int off = S->box_off[ip], nb = S->box_off[ip + 1] - off;
     const int lb0 = std::max(0, b0 - off), lb1 = std::min(nb, b1 - off);
@@ -586,7 +628,9 @@ int run_range(ctuppm_ctx* c, StepSet* S, hipStream_t s, int stage, int b0, int b
     const LevelTables& T = P->lt[S->level];
     ProbDev* rec = level_rec(P, S->level);
     int rc;
-    if (stage == kStFill) {
+    if (lists) {
+      rc = D.add(T, rf, zv, lb0, lb1);
+    } else if (stage == kStFill) {
       rc = R.add(T.recs[rf], T.fch + T.fpre[lb0], T.ftags, rec, T.fpre[lb1] - T.fpre[lb0]);
     } else if (stage >= kStBcX && stage <= kStBcZ) {
       const int d = stage - kStBcX;
@@ -598,7 +642,7 @@ int run_range(ctuppm_ctx* c, StepSet* S, hipStream_t s, int stage, int b0, int b
     }
     if (rc) return rc;
   }
-  return R.flush();
+  return lists ? D.flush() : R.flush();
 }
 
 int run_all(ctuppm_ctx* c, StepSet* S, hipStream_t s, int stage, bool timed, const StageArgs& A = StageArgs()) {
@@ -1215,12 +1259,9 @@ int recompute_fluxes(ctuppm_ctx* c, Problem* P, int slot, int rf) {
   if (off + box_scratch_bytes(B[b], ns) > P->ws_bytes)
     return fail(c, CTUPPM_ENOMEM, "problem %d: the scratch of box %d ends at byte %zu of a %zu-byte workspace",
                 P->id, b, off + box_scratch_bytes(B[b], ns), P->ws_bytes);
-  const LevelTables& T = P->lt[0];
-  const int k = stage_region(kStRiem3);
-  const std::vector<int>& pre = T.upre[2][k];
-  SegRun R{c, c->stream, kStRiem3, false, false, StageArgs()};
+  DirRun R{c, c->stream, kStRiem3, false, false, StageArgs()};
   R.A.rs = P->prm.riemann;
-  const int rc = R.add(T.recs[rf], T.units[2][k] + pre[b], nullptr, P->dP, pre[b + 1] - pre[b]);
+  const int rc = R.add(P->lt[0], rf, 2, b, b + 1);
   return rc ? rc : R.flush();
 }
 
@@ -2793,8 +2834,11 @@ int ctuppm_set_stage_planes(ctuppm_ctx* c, int stage, int planes) {
   if (stage < 0 || stage >= kNumStages || stage_region(stage) < 0)
     return fail(c, CTUPPM_EINVAL, "stage %d has no work units", stage);
   if (planes < 1 || planes > 64) return fail(c, CTUPPM_EINVAL, "planes per unit %d outside 1..64", planes);
-  c->region_planes[stage_region(stage)] = planes;
-  c->region_set[stage_region(stage)] = true;
+  for (int d = 0; d < (stage_by_lists(stage) ? 3 : 1); ++d) {
+    const int k = stage_by_lists(stage) ? stage_region_dir(stage, d) : stage_region(stage);
+    c->region_planes[k] = planes;
+    c->region_set[k] = true;
+  }
   for (auto& kv : c->probs) invalidate(c, kv.second.get());  // work lists and graphs depend on it
   return CTUPPM_OK;
 }

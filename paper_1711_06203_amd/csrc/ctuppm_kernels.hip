@@ -105,6 +105,16 @@ CTU_DEV void for_each_unit_dir(const Segs& L, F&& f) {
               [&](const March& M, const BoxRec& B) { f(d, M, B); });
   });
 }
+// Likewise, each direction with the work list of its own launch.
+template <class F>
+CTU_DEV void for_each_unit_dir(const DirSegs& L, F&& f) {
+  const int blocks = gridDim.x / 3, d = blockIdx.x / blocks;
+  for_each_chunk(L.beg[L.n][d], blockIdx.x - d * blocks, blocks, [&](int c) {
+    int s = 0;
+    while (s + 1 < L.n && c >= L.beg[s + 1][d]) ++s;
+    unit_body(L.s[s].work[d], L.s[s].boxes, c - L.beg[s][d], [&](const March& M, const BoxRec& B) { f(d, M, B); });
+  });
+}
 
 // Visit the tag chunks of a launch: f(chunk, its segment).
 template <class F>
@@ -982,11 +992,10 @@ CTU_DEV void riemann_unit(const March& M, const BoxRec& B) {
   const gdbl* __restrict__ ql = g.ql(B.scr, D);
   const gdbl* __restrict__ qr = g.qr(B.scr, D);
   gdbl* __restrict__ fn = g.fn(B.scr, D);
-  march(kCells1, B, M, [&](int i, int j, int k) {
+  march(D == 2 ? kFace2 : kCells1, B, M, [&](int i, int j, int k) {
     const int o = g.h(i, j, k);
     const int fa = D == 0 ? i : (D == 1 ? j : k);
     if (fa < 0) {
-      if (D == 2) return;  // a plane of its own: no line is partly written without it
       for (int m = 0; m < g.nv; ++m) fn[m * g.hcomp + o] = 0.0;
       return;
     }
@@ -1019,7 +1028,7 @@ __global__ __launch_bounds__(kBlock) void k_riemann(const Segs L) {
 // takes 8.0 us for the three instead of 20.1, a 256^3 level 1.223 ms instead
 // of 1.250.
 template <int RS>
-__global__ __launch_bounds__(kBlock) void k_riemann3(const Segs L) {
+__global__ __launch_bounds__(kBlock) void k_riemann3(const DirSegs L) {
   for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
     if (d == 0) riemann_unit<0, RS>(M, B);
     else if (d == 1) riemann_unit<1, RS>(M, B);
@@ -1262,17 +1271,14 @@ CTU_DEV void final_flux(const BoxRec& B, const Geo& g, CProb* P, int o, int fa, 
 
 // Stage 2 along A over faces 0..n (cells 0..n-1 across): final fluxes; the
 // threads cover whole rows (x over -1..n) and store zeros off the faces.
-// REGION: kFin0 + A, or kFin (one work list for the three directions, with a
-// row and a plane more than the faces along x, y or z take).
-template <int A, int RS, int REGION>
+template <int A, int RS>
 CTU_DEV void trans2_unit(const March& M, const BoxRec& B) {
   CProb* P = cprob(B.P);
   const Geo g(B.n, B.ns);
   gdbl* __restrict__ ff = g.ff(B.scr, A);
   int fb = 0;
   const int ilast = A == 0 ? B.n[0] : B.n[0] - 1;  // last x index holding a face
-  march(REGION, B, M, [&](int i, int j, int k) {
-    if (REGION == kFin && ((A != 1 && j >= B.n[1]) || (A != 2 && k >= B.n[2]))) return;
+  march(kFin0 + A, B, M, [&](int i, int j, int k) {
     final_flux<A, RS>(B, g, P, g.h(i, j, k), A == 0 ? i : (A == 1 ? j : k), i >= 0 && i <= ilast, ff, fb);
   });
   count(&B.P->cnt[3], (unsigned long long)fb);
@@ -1280,7 +1286,7 @@ CTU_DEV void trans2_unit(const March& M, const BoxRec& B) {
 
 template <int A, int RS>
 __global__ __launch_bounds__(kBlock) void k_trans2(const Segs L) {
-  for_each_unit(L, [&](const March& M, const BoxRec& B) { trans2_unit<A, RS, kFin0 + A>(M, B); });
+  for_each_unit(L, [&](const March& M, const BoxRec& B) { trans2_unit<A, RS>(M, B); });
 }
 
 // The three directions in one launch.  A 32^3 box takes 11 us instead of 26
@@ -1288,11 +1294,11 @@ __global__ __launch_bounds__(kBlock) void k_trans2(const Segs L) {
 // way.  With the units of all directions dealt to the XCDs as one list (a
 // direction per XCD at any time) it took 2.49 ms.
 template <int RS>
-__global__ __launch_bounds__(kBlock) void k_trans2_3(const Segs L) {
+__global__ __launch_bounds__(kBlock) void k_trans2_3(const DirSegs L) {
   for_each_unit_dir(L, [&](int d, const March& M, const BoxRec& B) {
-    if (d == 0) trans2_unit<0, RS, kFin>(M, B);
-    else if (d == 1) trans2_unit<1, RS, kFin>(M, B);
-    else trans2_unit<2, RS, kFin>(M, B);
+    if (d == 0) trans2_unit<0, RS>(M, B);
+    else if (d == 1) trans2_unit<1, RS>(M, B);
+    else trans2_unit<2, RS>(M, B);
   });
 }
 
@@ -1913,7 +1919,7 @@ const char* stage_name(int s) {
 
 hipError_t launch_stage(int stage, const Launch& L) {
   const Segs& G = L.segs;
-  if (G.n <= 0 || G.beg[G.n] <= 0) return hipSuccess;
+  if (L.grid <= 0) return hipSuccess;
   const dim3 grid(L.grid), block(kBlock);
   hipStream_t s = L.stream;
 #define CTU_LIM(K, D)                                                        \
@@ -1992,6 +1998,7 @@ hipError_t launch_stage(int stage, const Launch& L) {
         else k_trans1_all<0, false><<<grid, block, 0, s>>>(G);
       }
       break;
+#define CTU_LISTS(K) (L.rs ? K<1><<<grid, block, 0, s>>>(L.dirs) : K<0><<<grid, block, 0, s>>>(L.dirs))
 #define CTU_RS3(K) (L.rs ? K<1><<<grid, block, 0, s>>>(G) : K<0><<<grid, block, 0, s>>>(G))
 #define CTU_RS(K, D) (L.rs ? K<D, 1><<<grid, block, 0, s>>>(G) : K<D, 0><<<grid, block, 0, s>>>(G))
     case kStRiemX: CTU_RS(k_riemann, 0); break;
@@ -2003,12 +2010,13 @@ hipError_t launch_stage(int stage, const Launch& L) {
     case kStT2X: CTU_RS(k_trans2, 0); break;
     case kStT2Y: CTU_RS(k_trans2, 1); break;
     case kStT2Z: CTU_RS(k_trans2, 2); break;
-    case kStRiem3: CTU_RS3(k_riemann3); break;
-    case kStT2All: CTU_RS3(k_trans2_3); break;
+    case kStRiem3: CTU_LISTS(k_riemann3); break;
+    case kStT2All: CTU_LISTS(k_trans2_3); break;
     case kStT1Dir: CTU_RS3(k_trans1_dir); break;
     case kStTraceDir: CTU_LIM3(k_trace_dir); break;
     case kStReconDir: CTU_LIM3(k_recon_dir); break;
 #undef CTU_RS3
+#undef CTU_LISTS
 #undef CTU_RS
     case kStUpdate: 
       if (L.fin) k_update<true><<<grid, block, 0, s>>>(G, L.guard);
