@@ -90,15 +90,15 @@ def tune(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver], candidates: Iter
     return dict(out, cached=False)
 
 
-# Stages that a merged launch runs in the default mode: not timed on their own,
-# their settings stand (or follow the group they share) and are reported.
+# The settings that launches standing for several stages, or for another one,
+# take their work units from.
 MERGED: Dict[str, Tuple[str, ...]] = {
     "riemann_xyz": ("riemann_x", "riemann_y", "riemann_z"),
     "trans2_xyz": ("trans2_x", "trans2_y", "trans2_z"),
     "trace_dir": ("trace_xyz",),
     "trans1_dir": ("trans1_xyz",),
     "recon_dir": ("recon_xyz",),
-    "mol_flux_update": ("riemann_x", "riemann_y", "riemann_z", "mol_update"),
+    "mol_flux_update": ("mol_update",),
 }
 STAGE_CANDIDATES: Tuple[int, ...] = (1, 2, 4, 8)
 
@@ -128,7 +128,8 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
                 candidates: Iterable[int] = STAGE_CANDIDATES, steps: int = 3, cache: Optional[str] = CACHE,
                 use_cache: bool = True) -> dict:
     """Pick the planes per work unit of every stage group for these problems;
-    applies and returns {"planes": {stage: planes}, ...}.  The problems are
+    applies and returns {"planes": {stage: planes}, ...}, the settings whose
+    stages ran (a cached choice applies the same ones).  The problems are
     advanced by the timing steps."""
     key = "stages:" + signature(solvers)
     db = _load(cache)
@@ -137,16 +138,19 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
             ctx.set_stage_planes(st, p)
         return dict(db[key], cached=True)
     start = _stage_ms(ctx, solvers, steps)
-    groups: Dict[int, List[str]] = {}
+    groups: Dict[int, List[str]] = {}  # the stages timed that take a group's setting
     before: Dict[str, int] = {}
+    group: Dict[str, int] = {}
     for st in start:
-        try:
-            p, g = ctx.stage_planes(st)
-        except ctuppm.CtuError:
-            continue  # no work units (ghost fill, boundaries, dt, commit)
-        groups.setdefault(g, []).append(st)
-        before[st] = p
-    lead = {g: sts[0] for g, sts in groups.items()}
+        for name in MERGED.get(st, (st,)):
+            try:
+                before[name], g = ctx.stage_planes(name)
+            except ctuppm.CtuError:
+                continue  # no work units (ghost fill, boundaries, dt, commit)
+            group[name] = g
+            if st not in groups.setdefault(g, []):
+                groups[g].append(st)
+    lead = {g: next(name for name in group if group[name] == g) for g in groups}
     trials: Dict[int, Dict[str, float]] = {}
     for p in candidates:
         for g in groups:
@@ -162,13 +166,11 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
         ctx.set_stage_planes(lead[g], p)
     tuned = sum(_stage_ms(ctx, solvers, steps).values())
     base_total = sum(start.values())
-    planes = {st: best[g] for g, sts in groups.items() for st in sts}
+    planes = {name: best[g] for name, g in group.items()}
     if tuned > base_total:  # the groups interact through the caches: keep the starting setting
         for st, p in before.items():
             ctx.set_stage_planes(st, p)
         planes = dict(before)
-    for st in start:
-        planes.update({m: ctx.stage_planes(m)[0] for m in MERGED.get(st, ())})
     out = {"planes": planes, "ms_per_step": min(tuned, base_total), "start_ms_per_step": base_total,
            "trials": {str(p): t for p, t in trials.items()}, "signature": key,
            "when": time.strftime("%Y-%m-%dT%H:%M:%S")}
