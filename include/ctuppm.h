@@ -70,7 +70,8 @@ enum {
  * mirror the interior with the normal momentum negated, and every Riemann
  * problem on the wall face takes the mirror image of the inside state as the
  * outside state, so no mass crosses the wall); inflow (ghost cells hold
- * `inflow`, `inflow_X`). */
+ * `inflow`, `inflow_X`).  In a direction of fewer than 4 cells a mirror image
+ * beyond the opposite side goes through that side's boundary in turn. */
 enum { CTUPPM_BC_PERIODIC = 0, CTUPPM_BC_OUTFLOW = 1, CTUPPM_BC_REFLECT = 2, CTUPPM_BC_INFLOW = 3 };
 /* Step forms: one launch per stage per box; one persistent launch per stage
  * over the boxes of every problem stepped; the batched launches replayed from

@@ -1033,7 +1033,9 @@ static void inflow_cons(const orc_params *P, double *U) {
 /* Fill the ghost cells of a whole-domain grown array: first every ghost cell
  * whose periodic image is a valid cell, then the physical boundaries of the
  * non-periodic directions in the order x, y, z, each over the full grown extent
- * of the other two directions. */
+ * of the other two directions, layer by layer outwards: in a direction of fewer
+ * than NG cells a mirror image can be a ghost cell of the opposite side, of a
+ * layer nearer to the domain. */
 void orc_fill_domain(double *U, const int n[3], const orc_params *P) {
     const geom G = mkgeom(n);
     const geom *g = &G;
@@ -1055,15 +1057,20 @@ void orc_fill_domain(double *U, const int n[3], const orc_params *P) {
             }
     for (int d = 0; d < 3; ++d) {
         if (P->bc_lo[d] == BC_PERIODIC) continue;
-        for (int side = 0; side < 2; ++side) {
+        for (int l = 0; l < 2 * NG; ++l) {
+            const int side = l & 1, at = side == 0 ? -1 - l / 2 : n[d] + l / 2;
             const int bc = side == 0 ? P->bc_lo[d] : P->bc_hi[d];
             double Uin[MAXV];
             inflow_cons(P, Uin);
-            for (int k = -NG; k < n[2] + NG; ++k)
-                for (int j = -NG; j < n[1] + NG; ++j)
-                    for (int i = -NG; i < n[0] + NG; ++i) {
-                        int c[3] = {i, j, k};
-                        if (side == 0 ? c[d] >= 0 : c[d] < n[d]) continue;
+            int lo[3], hi[3];
+            for (int e = 0; e < 3; ++e) {
+                lo[e] = e == d ? at : -NG;
+                hi[e] = e == d ? at + 1 : n[e] + NG;
+            }
+            for (int k = lo[2]; k < hi[2]; ++k)
+                for (int j = lo[1]; j < hi[1]; ++j)
+                    for (int i = lo[0]; i < hi[0]; ++i) {
+                        const int c[3] = {i, j, k};
                         int s[3] = {i, j, k};
                         if (bc == BC_OUTFLOW) s[d] = side == 0 ? 0 : n[d] - 1;
                         else if (bc == BC_REFLECT) s[d] = side == 0 ? -c[d] - 1 : 2 * n[d] - 1 - c[d];

@@ -870,6 +870,7 @@ void bc_tags(const Problem* P, int l, int d, std::vector<BcTag>& bt, std::vector
         t.dir = d;
         t.side = side;
         t.bc = side == 0 ? P->prm.bc_lo[d] : P->prm.bc_hi[d];
+        t.bc_other = side == 0 ? P->prm.bc_hi[d] : P->prm.bc_lo[d];
         t.dom_lo = dlo[d];
         t.dom_hi = dhi[d];
         for (int m = 0; m < kNV + P->prm.nspec; ++m) t.inflow[m] = inflow_cons[m];

@@ -134,8 +134,9 @@ struct DirSegs {
 // inflow state instead.
 struct FillTag { int dst, src; int lo[3]; int ext[3]; int off[3]; int mode; };
 enum Map : int { kMapShift = 0, kMapClamp = 1, kMapMirror = 2, kMapNegate = 1 << 6, kMapInflow = 1 << 9 };
-// Physical boundary along dir on one side of the domain, over a box's grown cells.
-struct BcTag { int box; int dir; int side; int bc; int lo[3]; int ext[3]; int dom_lo, dom_hi; double inflow[kMaxV]; };
+// Physical boundary along dir on one side of the domain, over a box's grown cells
+// (bc_other: the opposite side's, for mirror images that lie beyond it).
+struct BcTag { int box; int dir; int side; int bc; int bc_other; int lo[3]; int ext[3]; int dom_lo, dom_hi; double inflow[kMaxV]; };
 
 // Two-level problems (ratio 2).  The fine level is one rectangle of fine
 // boxes covering coarse cells clo..chi; the coarse cells clo-3..chi+3 (the

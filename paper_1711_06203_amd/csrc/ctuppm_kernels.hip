@@ -229,7 +229,11 @@ __global__ __launch_bounds__(kBlock) void k_fill(const Segs L, int arr) {
 }
 
 // Physical boundary of one direction D: outflow copies the edge cell, reflect
-// mirrors with the normal momentum negated, inflow writes a fixed state.
+// mirrors with the normal momentum negated, inflow writes a fixed state.  In a
+// direction of fewer than four cells a mirror image can lie beyond the opposite
+// side: it then goes through that side's boundary, and so on, so every ghost
+// cell follows from a cell of the domain and none from another ghost cell that
+// this launch writes.
 template <int D>
 __global__ __launch_bounds__(kBlock) void k_bc(const Segs L, int arr) {
   for_each_tag_chunk(L, [&](const Chunk& ch, const Seg& S) {
@@ -245,21 +249,31 @@ __global__ __launch_bounds__(kBlock) void k_bc(const Segs L, int arr) {
     const Geo g(B.n, B.ns);
     gdbl* __restrict__ U = gp(state_arr(B, arr));
     const int di = g.g(x[0], x[1], x[2]);
-    if (T.bc == 3) {
-      for (int m = 0; m < g.nv; ++m) U[m * g.gcomp + di] = T.inflow[m];
+    int bc = T.bc, side = T.side;
+    int Xs = B.lo[D] + x[D];  // level index of the ghost cell, then of its source
+    bool neg = false;
+    while (bc == 2) {
+      Xs = side == 0 ? 2 * T.dom_lo - Xs - 1 : 2 * T.dom_hi + 1 - Xs;
+      neg = !neg;
+      if (Xs >= T.dom_lo && Xs <= T.dom_hi) break;
+      side ^= 1;
+      bc = T.bc_other;  // (two reflecting sides bring the image closer each time)
+    }
+    if (bc == 3) {
+      for (int m = 0; m < g.nv; ++m) {
+        const double v = T.inflow[m];
+        U[m * g.gcomp + di] = neg && m == 1 + D ? -v : v;
+      }
       return;
     }
-    const int X = B.lo[D] + x[D];  // level index of the ghost cell
-    int Xs;
-    if (T.bc == 1) Xs = T.side == 0 ? T.dom_lo : T.dom_hi;
-    else Xs = T.side == 0 ? 2 * T.dom_lo - X - 1 : 2 * T.dom_hi + 1 - X;
+    if (bc == 1) Xs = side == 0 ? T.dom_lo : T.dom_hi;
     int s[3] = {x[0], x[1], x[2]};
     s[D] = Xs - B.lo[D];
     const int si = g.g(s[0], s[1], s[2]);
 #pragma unroll
     for (int m = 0; m < kNV; ++m) {
       double v = U[m * g.gcomp + si];
-      if (T.bc == 2 && m == 1 + D) v = -v;
+      if (neg && m == 1 + D) v = -v;
       U[m * g.gcomp + di] = v;
     }
     for (int m = kNV; m < g.nv; ++m) U[m * g.gcomp + di] = U[m * g.gcomp + si];
