@@ -47,9 +47,13 @@ constexpr int kMaxRetryDepth = 3;   // ctuppm_step_checked halves a rejected ste
 // mix of ten problems, 19000 units: 154 -> 165 us).
 constexpr int kFinUnits = 2048;
 // That one launch pays up to twice as many units while boxes grown by their
-// ghost cells hold at most this many cells (96^3 step, one box 485.6 -> 480.5
-// us, boxes of 48^3 655 -> 642; 27 boxes of 32^3, 1.73 M cells: 931 -> 941,
-// 216 of 16^3, 2.99 M: 1135 -> 1182 by the third-order method of lines).
+// ghost cells hold at most this many cells (shear layer of 96^3 in one box,
+// periodic 492.8 -> 486.0 us a step, walls and outflow 505.3 -> 483.4; in boxes
+// of 48^3 510.5 -> 504.5 and 520.7 -> 506.5; by the third-order method of lines,
+// one box, 539.8 -> 517.8; 27 boxes of 32^3, 1.73 M cells: 931 -> 941, 216 of
+// 16^3, 2.99 M: 1135 -> 1182).  Its last block takes dt, and the update's
+// commits: beyond kFinUnits the commit alone gains nothing (483.4 in the update,
+// 485.2 launched), nor do both without the merged fill (492.8 launched, 491.2).
 constexpr long long kMapCells = 1600000;
 // Sets of at most this many stage-1 units leave CUs idle and take tracing and
 // stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
@@ -1641,7 +1645,7 @@ int enqueue_step_branched(ctuppm_ctx* c, StepSet* S, hipStream_t s, int guard) {
 int enqueue_step(ctuppm_ctx* c, StepSet* S, hipStream_t s, bool timed, int guard) {
   if (S->scheme != 0) return enqueue_mol(c, S, s, timed, guard);
   // every box its own scratch: the conversion's pass over the level also
-  // reduces the signal speed, and fills the ghost cells where all are copies.
+  // reduces the signal speed, and fills the ghost cells where all are mapped.
   // The other forms convert a box or a wave into its shared scratch right
   // before its stages, so only the CFL pass runs over all boxes first.
   const bool own = S->form == CTUPPM_FORM_BATCHED || S->form == kFormStatic || S->nboxes == 1;

@@ -33,9 +33,11 @@ CTU_DEV gdbl* gp(double* p) { return (gdbl*)p; }
 // (not kept in registers), through ds_* instructions.
 using ldbl = __attribute__((address_space(3))) volatile double;
 // The problem record as the stage kernels read it: through the constant
-// address space, since it is the same for a whole block and no kernel writes
-// the fields it reads this way (counters and the signal-speed maxima are
-// updated through the ordinary pointer).  The reads become scalar loads into
+// address space, since it is the same for a whole block and no unit of a
+// launch reads a field this way after it was written (counters and the
+// signal-speed maxima are updated through the ordinary pointer; where the last
+// unit of a problem's update commits, it writes cur, nsteps and fail_step when
+// all of that problem's units have ended).  The reads become scalar loads into
 // scalar registers; as flat loads they would also make a wave wait for its
 // earlier stores.
 using CProb = __attribute__((address_space(4))) const ProbDev;
@@ -2032,7 +2034,7 @@ hipError_t launch_stage(int stage, const Launch& L) {
 #undef CTU_RS3
 #undef CTU_LISTS
 #undef CTU_RS
-    case kStUpdate: 
+    case kStUpdate:
       if (L.fin) k_update<true><<<grid, block, 0, s>>>(G, L.guard);
       else k_update<false><<<grid, block, 0, s>>>(G, 0);
       break;
