@@ -9,7 +9,8 @@ through, and the rows per tile the units of a plane are grouped into.
 (``ctuppm_set_stage_planes``; stages over the same work region share one
 setting).  Every stage group is timed at every candidate from the library's
 per-stage timing of whole steps, each group takes its fastest, and the
-combination is kept only if a timed step confirms it.
+combination is kept only if a timed step confirms it, or if the starting
+setting is slower still once it is set.
 
 Every choice gives bitwise the same results (each cell's arithmetic is
 fixed), so the tuners only time: a few event-timed eager steps per candidate
@@ -167,11 +168,18 @@ def tune_stages(ctx: ctuppm.Context, solvers: Sequence[ctuppm.Solver],
     tuned = sum(_stage_ms(ctx, solvers, steps).values())
     base_total = sum(start.values())
     planes = {name: best[g] for name, g in group.items()}
-    if tuned > base_total:  # the groups interact through the caches: keep the starting setting
+    if tuned > base_total:
+        # the groups interact through the caches: keep the starting setting, unless
+        # it is slower once it is set (defaults left alone adapt to small sets)
         for st, p in before.items():
             ctx.set_stage_planes(st, p)
-        planes = dict(before)
-    out = {"planes": planes, "ms_per_step": min(tuned, base_total), "start_ms_per_step": base_total,
+        kept = sum(_stage_ms(ctx, solvers, steps).values())
+        if kept <= tuned:
+            planes, tuned = dict(before), kept
+        else:
+            for g, p in best.items():
+                ctx.set_stage_planes(lead[g], p)
+    out = {"planes": planes, "ms_per_step": tuned, "start_ms_per_step": base_total,
            "trials": {str(p): t for p, t in trials.items()}, "signature": key,
            "when": time.strftime("%Y-%m-%dT%H:%M:%S")}
     if cache:

@@ -112,3 +112,30 @@ def test_no_setting_of_a_stage_that_never_ran(tmp_path):
     solver = types.SimpleNamespace(prob=types.SimpleNamespace(boxes=[((0, 0, 0), (47, 47, 47))]))
     out = autotune.tune_stages(ctx, [solver], candidates=(1, 2, 4), steps=1, cache=str(tmp_path / "t.json"))
     assert out["planes"] == {"recon_xyz": 2, "mol_update": 1} and ctx.set_by_caller == {0, 9}
+
+
+class AdaptiveCtx(RouteCtx):
+    """A small set: the tracing runs at one plane, its best, until it is set; its
+    default reads 4.  A tuned step is a little slower than the start."""
+
+    def __init__(self):
+        super().__init__(limit=8)
+        self.planes[9] = 4
+        self.is_set = False
+
+    def set_stage_planes(self, st, p):
+        super().set_stage_planes(st, p)
+        self.is_set = True
+
+    def step(self, solvers, form, n):
+        p = self.planes[9] if self.is_set else 1
+        self.acc = {"trace_xyz": ({1: 5.0, 2: 6.0, 4: 8.0, 8: 9.0}[p] * n, n),
+                    "update": ((1.1 if self.is_set else 1.0) * n, n)}
+
+
+def test_the_starting_setting_is_kept_only_if_setting_it_is_no_slower():
+    ctx = AdaptiveCtx()
+    solver = types.SimpleNamespace(prob=types.SimpleNamespace(boxes=[((0, 0, 0), (47, 47, 47))]))
+    out = autotune.tune_stages(ctx, [solver], candidates=(1, 2, 4, 8), steps=1, cache=None)
+    assert out["planes"]["trace_xyz"] == 1 and ctx.planes[9] == 1
+    assert out["start_ms_per_step"] == 6.0 and out["ms_per_step"] == 6.1
