@@ -52,8 +52,9 @@ constexpr int kFinUnits = 2048;
 // of 48^3 510.5 -> 504.5 and 520.7 -> 506.5; by the third-order method of lines,
 // one box, 539.8 -> 517.8; 27 boxes of 32^3, 1.73 M cells: 931 -> 941, 216 of
 // 16^3, 2.99 M: 1135 -> 1182).  Its last block takes dt, and the update's
-// commits: beyond kFinUnits the commit alone gains nothing (483.4 in the update,
-// 485.2 launched), nor do both without the merged fill (492.8 launched, 491.2).
+// commits: beyond kFinUnits the commit alone makes no difference (periodic 486.0
+// in the update, 484.2 launched; walls 483.4, 485.2), and both without the merged
+// fill 0-1% (492.8 launched, 491.2; walls 505.3, 500.5).
 constexpr long long kMapCells = 1600000;
 // Sets of at most this many stage-1 units leave CUs idle and take tracing and
 // stage 1 by blocks of one direction each: step of one box of 16^3 46 -> 36
